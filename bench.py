@@ -36,7 +36,7 @@ BYTES_PER_LU = {"fp64": 288, "fp32": 144, "fp16": 76}
 PROFILE_TRAFFIC = {1: os.path.join(ROOT, "profiles", "fused_step_rt2048_fp32_pmc.txt"),
                    2: os.path.join(ROOT, "profiles", "fused_step2_rt2048_fp32_pmc.txt")}
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1507_03521_amd", "csrc", f)
-                  for f in ("qilbm_kernels.hip", "qilbm_device.hpp")]
+                  for f in ("qilbm_kernels.hip", "qilbm_rows.hpp", "qilbm_device.hpp")]
 
 
 def log(*a):

@@ -144,7 +144,7 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* params,
  * that captures lbm_step in a HIP graph for repeated replay must capture an
  * even number of launches, so that each replay starts from the buffer the
  * previous one ended in: with one step per launch an even nsteps, with two
- * steps per launch (lbm_set_pass) a multiple of 4. */
+ * steps per pass (lbm_set_pass) a multiple of 4. */
 lbm_status lbm_step(lbm_ctx* ctx, int64_t nsteps);
 
 /* Macroscopic fields at the current time t (Sec. III moments): phi, rho,
@@ -238,8 +238,10 @@ int64_t lbm_time(const lbm_ctx* ctx);
 lbm_status lbm_set_stream(lbm_ctx* ctx, void* stream);
 
 /* Launch shape of the one-step fused kernel: rows per workgroup segment
- * (0 = automatic: about 2.25 workgroups per resident slot, 16..32 rows).
- * Results do not depend on it. */
+ * (0 = automatic: about 2.25 workgroups per resident slot, 16..32 rows; a
+ * lattice whose two population buffers fit in 256 MiB then runs a tiled
+ * kernel instead of this row-sweeping one). Results do not depend on it
+ * beyond rounding. */
 lbm_status lbm_set_launch(lbm_ctx* ctx, int32_t seg_rows);
 
 /* Current one-step fused launch shape into out[4] (host): column strips (of
@@ -260,12 +262,16 @@ lbm_status lbm_launch_info(const lbm_ctx* ctx, int32_t out[4]);
  * steps = 1 (one launch per step) to rounding: the two kernels evaluate the
  * same expressions, but the compiler may fuse multiply-adds differently in
  * each. The exact integer invariant of the stored g holds in both. seg_rows: rows per workgroup
- * segment of the two-step kernel (0 = automatic: one round of workgroups).
+ * segment of the two-step kernel (0 = automatic: one round of workgroups; a
+ * lattice whose two population buffers fit in 256 MiB then runs a pair of
+ * FP64 or FP32 steps in tiled kernels instead, as one launch or, above about
+ * 256 x 256 nodes, as two).
  * LBM_EINVAL for steps other than 1 and 2, or seg_rows < 0. Applies to lbm_step only (not lbm_step_record, not
  * LBM_FLAG_UNFUSED). */
 lbm_status lbm_set_pass(lbm_ctx* ctx, int32_t steps, int32_t seg_rows);
 
-/* Shape of the kernel lbm_step launches for a pair of steps, into out[5]
+/* Shape of the row-sweeping kernel for a pair of steps, which lbm_step
+ * launches except where a tiled kernel runs (lbm_set_pass), into out[5]
  * (host): steps per pass, column strips (at most 242 columns for two steps),
  * segments per strip, rows per segment, threads per workgroup. */
 lbm_status lbm_pass_info(const lbm_ctx* ctx, int32_t out[5]);

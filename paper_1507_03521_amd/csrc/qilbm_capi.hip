@@ -162,7 +162,33 @@ lbm_status step_p(lbm_ctx* c, int64_t n, void* const* recs) {
   if (trt && recs) return LBM_EINVAL;
   const int64_t pl = c->geom.Ns;
   int64_t done = 0;
-  if (!unfused && c->pass_steps == 2 && n >= 2) {
+  // small lattices run as tiles, unless the caller has set the rows per
+  // segment of the row-sweeping kernel that would run otherwise
+  const bool small = !unfused && tile_fits<P>(c->geom);
+  const bool tile1 = small && c->seg_rows == 0;
+  if constexpr (P != P_F16) {
+    const bool tile2 = small && c->pass_steps == 2 && c->pass_seg_rows == 0;
+    if (tile2 && tile_steps<P>(c->geom) == 2) {
+      for (; n - done >= 2; done += 2) {
+        if (launch_step2_tile<P>(c->pop[c->cur], c->pop[c->cur ^ 1], k, c->geom,
+                                 recs ? recs[done] : nullptr, recs ? recs[done + 1] : nullptr,
+                                 c->stream, trt) != hipSuccess)
+          return LBM_EDEVICE;
+        c->cur ^= 1;
+        c->t += 2;
+      }
+    } else if (tile2) {
+      // a pair of steps is two launches
+      for (; done < n / 2 * 2; ++done) {
+        if (launch_step_tile<P>(c->pop[c->cur], c->pop[c->cur ^ 1], k, c->geom,
+                                recs ? recs[done] : nullptr, c->stream, trt) != hipSuccess)
+          return LBM_EDEVICE;
+        c->cur ^= 1;
+        c->t += 1;
+      }
+    }
+  }
+  if (!unfused && c->pass_steps == 2 && n - done >= 2) {
     const FusedShape sh2 = fused2_shape<P>(c->geom, c->pass_seg_rows, c->resident2);
     for (; n - done >= 2; done += 2) {
       void* r0 = recs ? recs[done] : nullptr;
@@ -184,6 +210,8 @@ lbm_status step_p(lbm_ctx* c, int64_t n, void* const* recs) {
     else if (unfused)
       e = launch_step_unfused<P>(c->pop[c->cur], c->pop[c->cur ^ 1], phi_f(c), mu_f(c), p_f(c),
                                  nullptr, k, c->geom, c->stream, trt);
+    else if (tile1)
+      e = launch_step_tile<P>(c->pop[c->cur], c->pop[c->cur ^ 1], k, c->geom, rec, c->stream, trt);
     else
       e = launch_step_fused<P>(c->pop[c->cur], c->pop[c->cur ^ 1], k, c->geom, sh, rec,
                                c->stream, trt);

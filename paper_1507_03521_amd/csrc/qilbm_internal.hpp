@@ -92,6 +92,20 @@ template <int P>
 hipError_t launch_step2_fused(const void* pin, void* pout, const Coef<typename PrecT<P>::T>& c,
                               const Geom& g, const FusedShape& sh, void* rec0, void* rec1,
                               hipStream_t s, bool trt = false);
+// Tiled kernels (qilbm_tile.hip) for lattices small enough for them
+// (tile_fits): one step per launch, or two (P_F64 and P_F32) where
+// tile_steps is 2. Records and trt as for the fused kernels.
+template <int P>
+bool tile_fits(const Geom& g);
+template <int P>
+int tile_steps(const Geom& g);
+template <int P>
+hipError_t launch_step_tile(const void* pin, void* pout, const Coef<typename PrecT<P>::T>& c,
+                            const Geom& g, void* rec, hipStream_t s, bool trt);
+template <int P>
+hipError_t launch_step2_tile(const void* pin, void* pout, const Coef<typename PrecT<P>::T>& c,
+                             const Geom& g, void* rec0, void* rec1, hipStream_t s, bool trt);
+
 template <int P>
 hipError_t launch_mass(const void* pop, void* phi, void* mu, double* part, int nred, double* out,
                        const Coef<typename PrecT<P>::T>& c, const Coef<double>& c64,

@@ -1,0 +1,538 @@
+// Forward step of small and medium lattices: a workgroup owns a tile of
+// TX x TY nodes and runs every stage of one step, or of two, over all its
+// nodes at once, where the row-sweeping kernels (qilbm_kernels.hip) run a
+// serial chain of row iterations.
+//
+// What bounds a small lattice is that chain: a row sweep of 16 rows and its
+// warm-up takes 31 iterations of four barriers (98 us per two FP64 steps at
+// 64 x 64, in four workgroups), while the lattice has work for a few
+// microseconds. Here a step is four barriers:
+//   A  phi over the tile and three nodes around it (pulled g),
+//   B  mu over the tile and two nodes around it,
+//   C  force, velocity, pressure over the tile and one node around it,
+//   D  collision of the tile,
+// with phi, mu and p in LDS planes and a node's populations in the registers
+// of the thread that collides it. Two steps in one launch run the same
+// stages twice, the first over the tile and four nodes around it; the words
+// between the two steps stay in LDS, in the storage format.
+//
+// Threads: the first NI own the interior (the nodes that collide), the next
+// NR the ring of one node around it, whose pressure needs pulled f; the
+// nodes further out only need phi and mu and are shared out over all threads,
+// those without an own node first, so that every stage is one round for most
+// wavefronts.
+#include "qilbm_internal.hpp"
+#include "qilbm_rows.hpp"
+
+namespace qilbm {
+
+namespace {
+
+// Where one node's populations come from: element offsets of the rows
+// y - 1, y, y + 1 and columns x - 1, x, x + 1 (periodic), and whether the
+// node lies on the bottom (lo) or top (hi) wall row.
+struct TileNode {
+  uint32_t r[3], c[3];
+  bool lo, hi;
+};
+
+// Node (x, y) given by coordinates that may lie up to 8 nodes outside the
+// lattice (nx, ny >= 3). Columns wrap. Rows wrap when periodic; beyond a wall
+// they are clamped to the wall row (such a node's values are never read).
+__device__ __forceinline__ TileNode tile_node(int x, int y, const Geom& g) {
+  TileNode k;
+  const unsigned nx = (unsigned)g.nx, ny = (unsigned)g.ny;
+  const unsigned xw = (unsigned)(x + 3 * g.nx) % nx;
+  k.c[0] = xw == 0 ? nx - 1 : xw - 1;
+  k.c[1] = xw;
+  k.c[2] = xw == nx - 1 ? 0 : xw + 1;
+  unsigned yw;
+  if (g.walls) yw = (unsigned)(y < 0 ? 0 : (y >= g.ny ? g.ny - 1 : y));
+  else yw = (unsigned)(y + 3 * g.ny) % ny;
+  k.lo = g.walls && yw == 0;
+  k.hi = g.walls && yw == ny - 1;
+  k.r[0] = (yw == 0 ? ny - 1 : yw - 1) * nx;
+  k.r[1] = yw * nx;
+  k.r[2] = (yw == ny - 1 ? 0 : yw + 1) * nx;
+  return k;
+}
+
+// Position h of the frame of D nodes around a W x H core: the D rows above,
+// the D rows below, then D + D columns of the core's rows.
+template <int W, int H, int D>
+__device__ __forceinline__ void frame_pos(int h, int& lx, int& ly) {
+  constexpr int RW = W + 2 * D, BAND = D * RW;
+  if (h < 2 * BAND) {
+    const int q = h / RW;
+    lx = h - q * RW - D;
+    ly = q < D ? q - D : H + q - D;
+  } else {
+    h -= 2 * BAND;
+    ly = h / (2 * D);
+    const int k = h - ly * (2 * D);
+    lx = k < D ? k - D : W + k - D;
+  }
+}
+template <int W, int H, int D>
+__host__ __device__ constexpr int frame_count() {
+  return (W + 2 * D) * (H + 2 * D) - W * H;
+}
+
+// Byte layout of a population buffer (see Pop): offset of direction I's
+// plane of f (G false) or g, its element size, and the byte of the element
+// that the value starts at.
+template <int P, bool G, int I>
+struct PlaneOf {
+  static constexpr uint32_t size = P == P_F64 ? 8 : (P == P_F32 ? 8 : (I == 0 ? (G ? 4 : 2) : 4));
+  __device__ __forceinline__ static uint32_t at(uint32_t Ns) {
+    if constexpr (P == P_F64) return (uint32_t)(G ? 9 + I : I) * 8u * Ns;
+    else if constexpr (P == P_F32) return (uint32_t)I * 8u * Ns;
+    else if constexpr (I == 0) return G ? 2u * Ns : 0u;
+    else return 6u * Ns + (uint32_t)(I - 1) * 4u * Ns;
+  }
+};
+
+// Reads direction I's word(s) of type S at the node's pull source, `part`
+// bytes into the element. EDGE: the node may lie on a wall row, where the
+// directions from beyond the wall take the node's own opposite population.
+template <typename S, int P, bool G, bool EDGE, int I>
+__device__ __forceinline__ S tile_pull(__amdgpu_buffer_rsrc_t rs, uint32_t Ns, const TileNode& k,
+                                       uint32_t part = 0) {
+  constexpr int cx = CXS(I), cy = CYS(I);
+  constexpr uint32_t size = PlaneOf<P, G, I>::size;
+  const uint32_t off = (k.r[1 - cy] + k.c[1 - cx]) * size + part;
+  if constexpr (EDGE && cy != 0) {
+    const bool wall = cy > 0 ? k.lo : k.hi;
+    const uint32_t own = PlaneOf<P, G, OPP(I)>::at(Ns) + (k.r[1] + k.c[1]) * size + part;
+    return buf_ld<S>(rs, wall ? own : PlaneOf<P, G, I>::at(Ns) + off, 0);
+  } else {
+    return buf_ld<S>(rs, off, PlaneOf<P, G, I>::at(Ns));
+  }
+}
+
+// A node's whole row of words.
+template <int P, bool EDGE, int I = 0>
+__device__ __forceinline__ void tile_load_dirs(__amdgpu_buffer_rsrc_t rs, uint32_t Ns,
+                                               const TileNode& k, Row<P>& row) {
+  if constexpr (I < 9) {
+    if constexpr (P == P_F64) {
+      row.f[I] = tile_pull<double, P, false, EDGE, I>(rs, Ns, k);
+      row.g[I] = tile_pull<double, P, true, EDGE, I>(rs, Ns, k);
+    } else if constexpr (P == P_F16 && I == 0) {
+      row.f0 = (uint32_t)__builtin_bit_cast(uint16_t,
+                                            tile_pull<__half, P, false, EDGE, 0>(rs, Ns, k));
+      row.w[0] = tile_pull<uint32_t, P, true, EDGE, 0>(rs, Ns, k);
+    } else {
+      row.w[I] = tile_pull<typename BufT<P>::R, P, true, EDGE, I>(rs, Ns, k);
+    }
+    tile_load_dirs<P, EDGE, I + 1>(rs, Ns, k, row);
+  }
+}
+
+// A node's g words alone (FP32: the high word of a pair, FP16 storage: the
+// high half), enough for phi.
+template <int P> struct GWord { using T = double; };
+template <> struct GWord<P_F32> { using T = int32_t; };
+template <> struct GWord<P_F16> { using T = uint32_t; };
+
+template <int P, bool EDGE, int I = 0>
+__device__ __forceinline__ void tile_load_g(__amdgpu_buffer_rsrc_t rs, uint32_t Ns,
+                                            const TileNode& k, typename GWord<P>::T w[9]) {
+  if constexpr (I < 9) {
+    if constexpr (P == P_F64) w[I] = tile_pull<double, P, true, EDGE, I>(rs, Ns, k);
+    else if constexpr (P == P_F32) w[I] = tile_pull<int32_t, P, true, EDGE, I>(rs, Ns, k, 4);
+    else w[I] = tile_pull<uint32_t, P, true, EDGE, I>(rs, Ns, k);
+    tile_load_g<P, EDGE, I + 1>(rs, Ns, k, w);
+  }
+}
+
+template <int P, int I = 0>
+__device__ __forceinline__ int32_t g_words_q(const typename GWord<P>::T w[9]) {
+  if constexpr (I < 9) {
+    int32_t q;
+    if constexpr (P == P_F32) q = w[I];
+    else q = BufPop<P>::template q_g<I>(w[I]);
+    return q + g_words_q<P, I + 1>(w);
+  } else {
+    return 0;
+  }
+}
+template <int P>
+__device__ __forceinline__ typename PrecT<P>::T g_words_phi(const typename GWord<P>::T w[9]) {
+  using T = typename PrecT<P>::T;
+  if constexpr (P == P_F64) return sum9(w);
+  else return T(g_words_q<P>(w)) * T(GQI);
+}
+
+// Stores a node's words at element n.
+template <int P, int I = 0>
+__device__ __forceinline__ void tile_store(__amdgpu_buffer_rsrc_t rs, uint32_t Ns, uint32_t n,
+                                           const Row<P>& row) {
+  if constexpr (I < 9) {
+    if constexpr (P == P_F64) {
+      buf_st<double>(row.f[I], rs, n * 8u, PlaneOf<P, false, I>::at(Ns));
+      buf_st<double>(row.g[I], rs, n * 8u, PlaneOf<P, true, I>::at(Ns));
+    } else if constexpr (P == P_F16 && I == 0) {
+      buf_st<__half>(__builtin_bit_cast(__half, (uint16_t)row.f0), rs, n * 2u, 0);
+      buf_st<uint32_t>(row.w[0], rs, n * 4u, PlaneOf<P, true, 0>::at(Ns));
+    } else {
+      buf_st<typename BufT<P>::R>(row.w[I], rs, n * PlaneOf<P, true, I>::size,
+                                  PlaneOf<P, true, I>::at(Ns));
+    }
+    tile_store<P, I + 1>(rs, Ns, n, row);
+  }
+}
+
+// Words between the two steps of a launch, direction-major over the first
+// step's interior.
+template <int P, int N> struct TileMid { typename BufT<P>::R w[9][N]; };
+template <int N> struct TileMid<P_F64, N> { double f[9][N]; double g[9][N]; };
+
+// Direction I's source in the intermediate words of node m (row pitch W):
+// the element, and the direction whose plane holds it.
+template <int P, int W, int N, bool EDGE, int I = 0>
+__device__ __forceinline__ void mid_row(const TileMid<P, N>& M, int m, bool lo, bool hi,
+                                        Row<P>& row) {
+  if constexpr (I < 9) {
+    constexpr int cx = CXS(I), cy = CYS(I);
+    int e = I * N + m - cy * W - cx;
+    if constexpr (EDGE && cy != 0) e = (cy > 0 ? lo : hi) ? OPP(I) * N + m : e;
+    if constexpr (P == P_F64) {
+      row.f[I] = (&M.f[0][0])[e];
+      row.g[I] = (&M.g[0][0])[e];
+    } else {
+      row.w[I] = (&M.w[0][0])[e];
+    }
+    mid_row<P, W, N, EDGE, I + 1>(M, m, lo, hi, row);
+  }
+}
+template <int P, int W, int N, bool EDGE, int I = 0>
+__device__ __forceinline__ void mid_g(const TileMid<P, N>& M, int m, bool lo, bool hi,
+                                      typename GWord<P>::T w[9]) {
+  if constexpr (I < 9) {
+    constexpr int cx = CXS(I), cy = CYS(I);
+    int e = I * N + m - cy * W - cx;
+    if constexpr (EDGE && cy != 0) e = (cy > 0 ? lo : hi) ? OPP(I) * N + m : e;
+    if constexpr (P == P_F64) w[I] = (&M.g[0][0])[e];
+    else w[I] = reinterpret_cast<const int32_t*>(&M.w[0][0])[2 * e + 1];
+    mid_g<P, W, N, EDGE, I + 1>(M, m, lo, hi, w);
+  }
+}
+template <int P, int N>
+__device__ __forceinline__ void mid_put(TileMid<P, N>& M, int m, const Row<P>& row) {
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    if constexpr (P == P_F64) {
+      M.f[i][m] = row.f[i];
+      M.g[i][m] = row.g[i];
+    } else {
+      M.w[i][m] = row.w[i];
+    }
+  }
+}
+
+// phi, mu and p of the largest stage, rows of PX nodes.
+template <typename T, int PX, int PY>
+struct TileRings {
+  T phi[PY * PX];
+  T mu[PY * PX];
+  T p[PY * PX];
+};
+
+// 3x3 neighbourhood of element e; beyond a wall the mirrored row is e's own.
+template <typename T, int PX>
+__device__ __forceinline__ void tile3x3(const T* a, int e, bool lo, bool hi, T v[3][3]) {
+  const int em = lo ? e : e - PX, ep = hi ? e : e + PX;
+#pragma unroll
+  for (int d = -1; d <= 1; ++d) {
+    v[0][d + 1] = a[em + d];
+    v[1][d + 1] = a[e + d];
+    v[2][d + 1] = a[ep + d];
+  }
+}
+
+template <int K, int P, int N> struct MidOf { using T = TileMid<P, N>; };
+template <int P, int N> struct MidOf<1, P, N> { struct T {}; };
+
+// One step over an interior of IX x IY nodes whose corner is lattice node
+// (bx, by). FROM_MID: the populations come from M (pitch and extent of the
+// previous step's interior, four nodes larger on each side), else from `in`.
+// TO_MID: the post-collision words go to M, else the nodes of the lattice
+// (x < nx, y < ny) go to `out`. LDS element of interior node (lx, ly):
+// (ly + 3) PX + lx + 3.
+template <int P, int IX, int IY, int PX, int PY, int NT, int NM_, bool FROM_MID, bool TO_MID,
+          bool EDGE, bool TRT, typename MID>
+__device__ __forceinline__ void tile_phase(__amdgpu_buffer_rsrc_t rin, __amdgpu_buffer_rsrc_t rout,
+                                           const Coef<typename PrecT<P>::T>& c, const Geom& g,
+                                           int bx, int by, int ox, int TXr, int TYr,
+                                           typename PrecT<P>::T* rec,
+                                           TileRings<typename PrecT<P>::T, PX, PY>& L, MID& M) {
+  using T = typename PrecT<P>::T;
+  constexpr int NI = IX * IY, NR = frame_count<IX, IY, 1>(), NP = NI + NR;
+  constexpr int NPHI = frame_count<IX + 2, IY + 2, 2>(), NMU = frame_count<IX + 2, IY + 2, 1>();
+  constexpr int MW = IX + 8;          // pitch of M when FROM_MID
+  static_assert(NP <= NT, "one own node per thread");
+  const int t = threadIdx.x;
+  const uint32_t Ns = (uint32_t)g.Ns;
+  const int slot = t >= NP ? t - NP : t + NT - NP;
+  // own node
+  int lx = 0, ly = 0;
+  if (t < NI) {
+    ly = t / IX;
+    lx = t - ly * IX;
+  } else if (t < NP) {
+    frame_pos<IX, IY, 1>(t - NI, lx, ly);
+  }
+  const int e = (ly + 3) * PX + lx + 3;
+  const TileNode k = tile_node(bx + lx, by + ly, g);
+  const bool in_tile = t < NI && lx >= ox && lx < ox + TXr && ly >= ox && ly < ox + TYr;
+  const bool owns = in_tile && bx + lx < g.nx && by + ly < g.ny;
+  const int64_t n = (int64_t)k.r[1] + k.c[1];
+  Row<P> row;
+  T ph = T(0);
+  int32_t phi_q = 0;
+  // A
+  if (t < NP) {
+    if constexpr (FROM_MID) mid_row<P, MW, NM_, EDGE>(M, (ly + 4) * MW + lx + 4, k.lo, k.hi, row);
+    else tile_load_dirs<P, EDGE>(rin, Ns, k, row);
+  }
+  for (int h = slot; h < NPHI; h += NT) {
+    int hx, hy;
+    frame_pos<IX + 2, IY + 2, 2>(h, hx, hy);
+    hx -= 1;
+    hy -= 1;
+    const TileNode kh = tile_node(bx + hx, by + hy, g);
+    typename GWord<P>::T w[9];
+    if constexpr (FROM_MID) mid_g<P, MW, NM_, EDGE>(M, (hy + 4) * MW + hx + 4, kh.lo, kh.hi, w);
+    else tile_load_g<P, EDGE>(rin, Ns, kh, w);
+    L.phi[(hy + 3) * PX + hx + 3] = g_words_phi<P>(w);
+  }
+  if (t < NP) {
+    ph = row_phi<P>(row, phi_q);
+    L.phi[e] = ph;
+  }
+  __syncthreads();
+  // B
+  T mu = T(0);
+  if (t < NP) {
+    T v[3][3], gx, gy, lap;
+    tile3x3<T, PX>(L.phi, e, k.lo, k.hi, v);
+    stencil(v, gx, gy, lap);
+    mu = mu_bulk(v[1][1], c) - c.kappa * lap;
+    L.mu[e] = mu;
+  }
+  for (int h = slot; h < NMU; h += NT) {
+    int hx, hy;
+    frame_pos<IX + 2, IY + 2, 1>(h, hx, hy);
+    hx -= 1;
+    hy -= 1;
+    const int y = by + hy;
+    const int eh = (hy + 3) * PX + hx + 3;
+    const bool lo = g.walls && y <= 0, hi = g.walls && y >= g.ny - 1;
+    T v[3][3], gx, gy, lap;
+    tile3x3<T, PX>(L.phi, eh, lo, hi, v);
+    stencil(v, gx, gy, lap);
+    L.mu[eh] = mu_bulk(v[1][1], c) - c.kappa * lap;
+  }
+  __syncthreads();
+  // C
+  Macro<T> m;
+  T f[9], gg[9];
+  if (t < NP) {
+    row_unpack<P>(row, f, gg);
+    T S, jx, jy;
+    moments9(f, S, jx, jy);
+    T v[3][3], gphx, gphy, lapphi, gmux, gmuy, lapmu;
+    tile3x3<T, PX>(L.phi, e, k.lo, k.hi, v);
+    stencil(v, gphx, gphy, lapphi);
+    tile3x3<T, PX>(L.mu, e, k.lo, k.hi, v);
+    stencil(v, gmux, gmuy, lapmu);
+    macro_node(ph, mu, gphx, gphy, gmux, gmuy, lapmu, S, jx, jy, c, m);
+    L.p[e] = m.p;
+    if (rec && owns) {
+      rec[n] = ph;
+      rec[g.Ns + n] = mu;
+      rec[2 * g.Ns + n] = m.p;
+      rec[3 * g.Ns + n] = S;
+      rec[4 * g.Ns + n] = jx;
+      rec[5 * g.Ns + n] = jy;
+    }
+  }
+  __syncthreads();
+  // D
+  if (t < NI) {
+    T v[3][3], dpx, dpy, lapp;
+    tile3x3<T, PX>(L.p, e, k.lo, k.hi, v);
+    stencil(v, dpx, dpy, lapp);
+    if constexpr (TRT) collide_node_trt(f, gg, m, dpx, dpy, c);
+    else collide_node(f, gg, m, dpx, dpy, c);
+    Row<P> o;
+    row_pack<P>(f, gg, phi_q, o);
+    if constexpr (TO_MID) mid_put<P, NM_>(M, ly * IX + lx, o);
+    else if (owns) tile_store<P>(rout, Ns, (uint32_t)n, o);
+  }
+}
+
+// K steps of the lattice; tile (i, j) starts at node (i TX, j TY). Beyond the
+// lattice's last column a tile goes on with the wrapped columns (computed,
+// not stored); so it does beyond the last row when periodic.
+// rec0, rec1: records of the states the steps start from, or null. Whether
+// they are written is a uniform branch and not a variant of the kernel: the
+// compiler contracts multiply-adds per kernel, and a recording replay must
+// reproduce the plain steps bit for bit.
+template <int P, int K, int TX, int TY, int NT, bool TRT>
+__global__ __launch_bounds__(NT) void k_tile(Pop<P> in, Pop<P> out, Coef<typename PrecT<P>::T> c,
+                                             Geom g, int ntx, uint32_t bytes,
+                                             typename PrecT<P>::T* rec0,
+                                             typename PrecT<P>::T* rec1) {
+  using T = typename PrecT<P>::T;
+  static_assert(K == 1 || K == 2, "steps per launch");
+  constexpr int O = 4 * (K - 1);                 // first step's interior beyond the tile
+  constexpr int PX = TX + 2 * O + 6, PY = TY + 2 * O + 6;
+  constexpr int NM_ = (TX + 2 * O) * (TY + 2 * O);
+  __shared__ TileRings<T, PX, PY> L;
+  __shared__ typename MidOf<K, P, NM_>::T M;
+  const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(in.base, 0, (int)bytes, BUF_WORD3);
+  const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(out.base, 0, (int)bytes, BUF_WORD3);
+  // consecutive tiles, which share halo nodes, on one XCD
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int ty = tile / ntx, tx = tile - ty * ntx;
+  const int x0 = tx * TX, y0 = ty * TY;
+  // the wall rows are within reach of this tile's pulls (uniform)
+  const bool edge = g.walls && (y0 - O - 3 <= 0 || y0 + TY + O + 3 >= g.ny);
+  if constexpr (K == 2) {
+    if (edge) {
+      tile_phase<P, TX + 8, TY + 8, PX, PY, NT, NM_, false, true, true, TRT>(
+          rin, rout, c, g, x0 - 4, y0 - 4, 4, TX, TY, rec0, L, M);
+      __syncthreads();
+      tile_phase<P, TX, TY, PX, PY, NT, NM_, true, false, true, TRT>(
+          rin, rout, c, g, x0, y0, 0, TX, TY, rec1, L, M);
+    } else {
+      tile_phase<P, TX + 8, TY + 8, PX, PY, NT, NM_, false, true, false, TRT>(
+          rin, rout, c, g, x0 - 4, y0 - 4, 4, TX, TY, rec0, L, M);
+      __syncthreads();
+      tile_phase<P, TX, TY, PX, PY, NT, NM_, true, false, false, TRT>(
+          rin, rout, c, g, x0, y0, 0, TX, TY, rec1, L, M);
+    }
+  } else {
+    if (edge)
+      tile_phase<P, TX, TY, PX, PY, NT, NM_, false, false, true, TRT>(
+          rin, rout, c, g, x0, y0, 0, TX, TY, rec0, L, M);
+    else
+      tile_phase<P, TX, TY, PX, PY, NT, NM_, false, false, false, TRT>(
+          rin, rout, c, g, x0, y0, 0, TX, TY, rec0, L, M);
+  }
+}
+
+// ------------------------------------------------------------- dispatch
+// Measured on MI355X (us per step, row-sweeping kernel -> tiles; fp64 / fp32
+// at two steps per pass, fp16 storage at one):
+//   64 x 64      49.4 -> 3.75   33.2 -> 3.17   34.3 -> 4.44
+//   128 x 128    53.0 -> 4.27   35.2 -> 3.48   35.7 -> 4.52
+//   256 x 256    52.8 -> 6.01   35.4 -> 4.31   35.3 -> 4.99
+//   256 x 1024   53.1 -> 16.8   35.7 -> 9.55   36.1 -> 8.45
+//   701 x 1333   59.1 -> 68.4   38.2 -> 25.3   39.1 -> 21.8
+//   1001 x 2003   121 -> 182    53.1 -> 83.0   58.4 -> 43.7
+//   2048 x 2048   210 -> 317    91.6 -> 179     103 -> 116
+constexpr int CUS = 256;    // compute units: a grid of at most as many tiles is one round
+
+// Two steps per launch pay while one round of workgroups covers the lattice:
+// launches and loads are halved, and the second collision of the halo runs on
+// compute units that would idle. The smallest tile that does it in one round
+// is the fastest: 8 x 4 up to 64 x 128, 16 x 4 up to 128 x 128, 32 x 8 up to
+// 256 x 256 (fp64, 64 x 64: 3.75, 3.96, 5.20 us; 128 x 128: 4.92, 4.27, 5.44;
+// 256 x 256: 10.0, 11.2, 6.01). Beyond, the doubled halo costs more than a
+// launch (256 x 1024, fp64: two steps 18.2, one 16.8) and a pair of steps is
+// two launches.
+int tiles(const Geom& g, int tx, int ty) {
+  const int64_t n = ((int64_t)(g.nx + tx - 1) / tx) * ((g.ny + ty - 1) / ty);
+  return n > INT32_MAX ? INT32_MAX : (int)n;
+}
+
+template <int P, int K, int TX, int TY, int NT, bool TRT>
+void launch_tile(const void* pin, void* pout, const Coef<typename PrecT<P>::T>& c, const Geom& g,
+                 void* rec0, void* rec1, hipStream_t s) {
+  using T = typename PrecT<P>::T;
+  const Pop<P> i{(char*)pin, g.Ns}, o{(char*)pout, g.Ns};
+  hipLaunchKernelGGL((k_tile<P, K, TX, TY, NT, TRT>), dim3(tiles(g, TX, TY)), dim3(NT), 0, s,
+                     i, o, c, g, (g.nx + TX - 1) / TX, (uint32_t)pop_bytes(P, g.Ns), (T*)rec0,
+                     (T*)rec1);
+}
+
+template <int P, int K, int TX, int TY, int NT>
+hipError_t launch_tile_variant(const void* pin, void* pout, const Coef<typename PrecT<P>::T>& c,
+                               const Geom& g, void* rec0, void* rec1, hipStream_t s, bool trt) {
+  if (trt && (rec0 || rec1)) return hipErrorInvalidValue;       // no recording TRT variant
+  if (trt) launch_tile<P, K, TX, TY, NT, true>(pin, pout, c, g, nullptr, nullptr, s);
+  else launch_tile<P, K, TX, TY, NT, false>(pin, pout, c, g, rec0, rec1, s);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// Tiles while both population buffers together stay within the 256 MB
+// Infinity Cache: a tile reads its halo again from L2 and beyond, which is
+// cheap only there. Past it the row sweep, which moves the state once per two
+// steps, is faster: fp64 at 934 k nodes (269 MB) 59 us against 61..68, at
+// 490 k (141 MB) 58 against 27; fp32 at 2.0 M nodes (289 MB) 53 against 69,
+// at 1.2 M (174 MB) 45 against 33; fp16 storage at 4.2 M nodes (319 MB) 103
+// against 116, at 2.0 M (152 MB) 58 against 44. The limit also keeps every
+// byte offset in a buffer below 2^31.
+template <int P>
+bool tile_fits(const Geom& g) {
+  return 2 * pop_bytes(P, g.Ns) <= (int64_t)256 << 20;
+}
+
+template <int P>
+int tile_steps(const Geom& g) {
+  return tiles(g, 32, 8) <= CUS ? 2 : 1;
+}
+
+template <int P>
+hipError_t launch_step_tile(const void* pin, void* pout, const Coef<typename PrecT<P>::T>& c,
+                            const Geom& g, void* rec, hipStream_t s, bool trt) {
+  // one step: small tiles spread a small lattice over more compute units;
+  // a large one takes tiles with less halo. FP64 runs best in workgroups of
+  // 256 (its 114 registers allow four of them per compute unit): 256 x 1024
+  // 16.8 us in 32 x 4 tiles, 17.7 in 32 x 8
+  if constexpr (P == P_F64) {
+    if (tiles(g, 16, 4) <= CUS)
+      return launch_tile_variant<P, 1, 16, 4, 128>(pin, pout, c, g, rec, nullptr, s, trt);
+    return launch_tile_variant<P, 1, 32, 4, 256>(pin, pout, c, g, rec, nullptr, s, trt);
+  } else {
+    if (tiles(g, 16, 8) <= CUS)
+      return launch_tile_variant<P, 1, 16, 8, 256>(pin, pout, c, g, rec, nullptr, s, trt);
+    return launch_tile_variant<P, 1, 32, 8, 512>(pin, pout, c, g, rec, nullptr, s, trt);
+  }
+}
+
+template <int P>
+hipError_t launch_step2_tile(const void* pin, void* pout, const Coef<typename PrecT<P>::T>& c,
+                             const Geom& g, void* rec0, void* rec1, hipStream_t s, bool trt) {
+  if (tiles(g, 8, 4) <= CUS)
+    return launch_tile_variant<P, 2, 8, 4, 256>(pin, pout, c, g, rec0, rec1, s, trt);
+  if (tiles(g, 16, 4) <= CUS)
+    return launch_tile_variant<P, 2, 16, 4, 384>(pin, pout, c, g, rec0, rec1, s, trt);
+  return launch_tile_variant<P, 2, 32, 8, 832>(pin, pout, c, g, rec0, rec1, s, trt);
+}
+
+#define QILBM_INSTANTIATE(P)                                                                     \
+  template bool tile_fits<P>(const Geom&);                                                       \
+  template hipError_t launch_step_tile<P>(const void*, void*, const Coef<PrecT<P>::T>&,          \
+                                          const Geom&, void*, hipStream_t, bool);
+
+QILBM_INSTANTIATE(P_F64)
+QILBM_INSTANTIATE(P_F32)
+QILBM_INSTANTIATE(P_F16)
+#undef QILBM_INSTANTIATE
+
+#define QILBM_INSTANTIATE2(P)                                                                    \
+  template int tile_steps<P>(const Geom&);                                                       \
+  template hipError_t launch_step2_tile<P>(const void*, void*, const Coef<PrecT<P>::T>&,         \
+                                           const Geom&, void*, void*, hipStream_t, bool);
+
+QILBM_INSTANTIATE2(P_F64)
+QILBM_INSTANTIATE2(P_F32)
+#undef QILBM_INSTANTIATE2
+
+}  // namespace qilbm
