@@ -32,7 +32,11 @@ struct AdjointState {
   char* fld = nullptr;                // forward phi, mu, p
   char* afld = nullptr;               // A_NFIELDS planes
   double* part = nullptr;             // 4 regions x nred x 4
-  double* acc = nullptr;              // running totals [4] + final outputs [4]
+  double* acc = nullptr;              // totals of tpart [4] and of part [4]
+  // parameter sums of the tiled adjoint step, 4 per tile, in the space of
+  // afld (which only the three-kernel step uses); ntiles 0: no tiled step
+  double* tpart = nullptr;
+  int ntiles = 0;
   int nred = 0;
   int resident = 0;                   // fused adjoint workgroups resident at once
 };
@@ -47,5 +51,16 @@ struct CtxView {
 };
 
 CtxView ctx_view(lbm_ctx* c);
+
+// Tiled adjoint step (qilbm_adjoint_tile.hip) of lattices small enough for it
+// (adj_tile_fits): replaces the cotangents hin by hout and adds each tile's
+// four parameter sums to its slot of part (adj_tile_count tiles).
+template <typename T>
+bool adj_tile_fits(const Geom& g);
+template <typename T>
+int adj_tile_count(const Geom& g);
+template <typename T>
+hipError_t launch_adj_tile(const void* rec, const void* hin, void* hout, double* part,
+                           const Coef<T>& c, const Geom& g, hipStream_t s);
 
 }  // namespace qilbm

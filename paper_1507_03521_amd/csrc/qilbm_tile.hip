@@ -23,60 +23,11 @@
 // wavefronts.
 #include "qilbm_internal.hpp"
 #include "qilbm_rows.hpp"
+#include "qilbm_tile.hpp"
 
 namespace qilbm {
 
 namespace {
-
-// Where one node's populations come from: element offsets of the rows
-// y - 1, y, y + 1 and columns x - 1, x, x + 1 (periodic), and whether the
-// node lies on the bottom (lo) or top (hi) wall row.
-struct TileNode {
-  uint32_t r[3], c[3];
-  bool lo, hi;
-};
-
-// Node (x, y) given by coordinates that may lie up to 8 nodes outside the
-// lattice (nx, ny >= 3). Columns wrap. Rows wrap when periodic; beyond a wall
-// they are clamped to the wall row (such a node's values are never read).
-__device__ __forceinline__ TileNode tile_node(int x, int y, const Geom& g) {
-  TileNode k;
-  const unsigned nx = (unsigned)g.nx, ny = (unsigned)g.ny;
-  const unsigned xw = (unsigned)(x + 3 * g.nx) % nx;
-  k.c[0] = xw == 0 ? nx - 1 : xw - 1;
-  k.c[1] = xw;
-  k.c[2] = xw == nx - 1 ? 0 : xw + 1;
-  unsigned yw;
-  if (g.walls) yw = (unsigned)(y < 0 ? 0 : (y >= g.ny ? g.ny - 1 : y));
-  else yw = (unsigned)(y + 3 * g.ny) % ny;
-  k.lo = g.walls && yw == 0;
-  k.hi = g.walls && yw == ny - 1;
-  k.r[0] = (yw == 0 ? ny - 1 : yw - 1) * nx;
-  k.r[1] = yw * nx;
-  k.r[2] = (yw == ny - 1 ? 0 : yw + 1) * nx;
-  return k;
-}
-
-// Position h of the frame of D nodes around a W x H core: the D rows above,
-// the D rows below, then D + D columns of the core's rows.
-template <int W, int H, int D>
-__device__ __forceinline__ void frame_pos(int h, int& lx, int& ly) {
-  constexpr int RW = W + 2 * D, BAND = D * RW;
-  if (h < 2 * BAND) {
-    const int q = h / RW;
-    lx = h - q * RW - D;
-    ly = q < D ? q - D : H + q - D;
-  } else {
-    h -= 2 * BAND;
-    ly = h / (2 * D);
-    const int k = h - ly * (2 * D);
-    lx = k < D ? k - D : W + k - D;
-  }
-}
-template <int W, int H, int D>
-__host__ __device__ constexpr int frame_count() {
-  return (W + 2 * D) * (H + 2 * D) - W * H;
-}
 
 // Byte layout of a population buffer (see Pop): offset of direction I's
 // plane of f (G false) or g, its element size, and the byte of the element
@@ -238,18 +189,6 @@ struct TileRings {
   T mu[PY * PX];
   T p[PY * PX];
 };
-
-// 3x3 neighbourhood of element e; beyond a wall the mirrored row is e's own.
-template <typename T, int PX>
-__device__ __forceinline__ void tile3x3(const T* a, int e, bool lo, bool hi, T v[3][3]) {
-  const int em = lo ? e : e - PX, ep = hi ? e : e + PX;
-#pragma unroll
-  for (int d = -1; d <= 1; ++d) {
-    v[0][d + 1] = a[em + d];
-    v[1][d + 1] = a[e + d];
-    v[2][d + 1] = a[ep + d];
-  }
-}
 
 template <int K, int P, int N> struct MidOf { using T = TileMid<P, N>; };
 template <int P, int N> struct MidOf<1, P, N> { struct T {}; };
@@ -434,8 +373,6 @@ __global__ __launch_bounds__(NT) void k_tile(Pop<P> in, Pop<P> out, Coef<typenam
 //   701 x 1333   59.1 -> 68.4   38.2 -> 25.3   39.1 -> 21.8
 //   1001 x 2003   121 -> 182    53.1 -> 83.0   58.4 -> 43.7
 //   2048 x 2048   210 -> 317    91.6 -> 179     103 -> 116
-constexpr int CUS = 256;    // compute units: a grid of at most as many tiles is one round
-
 // Two steps per launch pay while one round of workgroups covers the lattice:
 // launches and loads are halved, and the second collision of the halo runs on
 // compute units that would idle. The smallest tile that does it in one round
@@ -444,11 +381,6 @@ constexpr int CUS = 256;    // compute units: a grid of at most as many tiles is
 // 256 x 256: 10.0, 11.2, 6.01). Beyond, the doubled halo costs more than a
 // launch (256 x 1024, fp64: two steps 18.2, one 16.8) and a pair of steps is
 // two launches.
-int tiles(const Geom& g, int tx, int ty) {
-  const int64_t n = ((int64_t)(g.nx + tx - 1) / tx) * ((g.ny + ty - 1) / ty);
-  return n > INT32_MAX ? INT32_MAX : (int)n;
-}
-
 template <int P, int K, int TX, int TY, int NT, bool TRT>
 void launch_tile(const void* pin, void* pout, const Coef<typename PrecT<P>::T>& c, const Geom& g,
                  void* rec0, void* rec1, hipStream_t s) {

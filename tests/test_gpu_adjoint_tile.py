@@ -1,0 +1,62 @@
+"""Tiled adjoint step of small and medium lattices against the three-kernel
+adjoint (LBM_FLAG_UNFUSED) on the same record and cotangents; the existing
+adjoint tests compare the same step with the oracle at small sizes.
+
+The tile shape goes by the number of tiles (8 x 4, 16 x 4, 32 x 8, then 16 x 8
+for FP64), up to the lattices whose two cotangent buffers and record fill
+256 MiB. Sizes sit on both sides of each change, on whole tiles and one node
+off them, below the halo's width, and at the largest FP64 lattice of the range
+and the next one that sweeps rows instead.
+
+Tolerances (max |a - b| / max |b|) are those of the row-sweeping adjoint
+against the three kernels: FP64 1e-13, FP32 1e-5 for the cotangents; the
+parameter sums, which cancel over random cotangents, 1e-10 and 1e-3.
+"""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"fp64": (1e-13, 1e-10), "fp32": (1e-5, 1e-3)}
+UNFUSED = 2
+
+
+@pytest.mark.parametrize("nx,ny,bc,precision", [
+    (3, 3, wl.PERIODIC, "fp64"), (3, 4, wl.WALLS_Y, "fp32"), (8, 4, wl.WALLS_Y, "fp64"),
+    (9, 5, wl.WALLS_Y, "fp64"), (64, 128, wl.WALLS_Y, "fp64"), (65, 128, wl.PERIODIC, "fp32"),
+    (129, 65, wl.WALLS_Y, "fp64"), (128, 128, wl.WALLS_Y, "fp32"), (129, 129, wl.WALLS_Y, "fp64"),
+    (256, 256, wl.PERIODIC, "fp64"), (257, 257, wl.WALLS_Y, "fp64"), (257, 255, wl.WALLS_Y, "fp32"),
+    (892, 892, wl.WALLS_Y, "fp64"), (895, 893, wl.WALLS_Y, "fp64")])
+def test_tiled_adjoint_matches_three_kernels(nx, ny, bc, precision):
+    from paper_1507_03521_amd import Lattice
+    print(f"case adjoint tiles {nx}x{ny} bc={bc} {precision}", flush=True)
+    pb = wl.droplet64().with_(nx=nx, ny=ny, bc=bc, gx=1e-5, gy=-2e-5, rho_ref=0.5)
+    f, g = wl.random_state(nx, ny, seed=nx + 3 * ny)
+    rng = np.random.default_rng(5)
+    # cotangents of one sign, so that the parameter sums keep their digits
+    fbar, gbar = rng.random((9, ny, nx)), rng.random((9, ny, nx))
+    out = []
+    record = None
+    for flags in (0, UNFUSED):
+        lat = Lattice(pb.as_dict(), np.full((ny, nx), 0.5), precision=precision, flags=flags,
+                      device="cuda:0")
+        if record is None:
+            lat.set_state(f, g)
+            record = lat.step_record()
+        lat.adjoint_begin(torch.zeros((ny, nx), dtype=torch.float64, device="cuda:0"))
+        for _ in range(2):                       # the second must start from cleared sums
+            lat.adjoint_set(fbar, gbar)
+            lat.adjoint_step_record(record)
+            lat.adjoint_step_record(record)
+        out.append(lat.adjoint_get())
+        lat.close()
+    (f1, g1, s1, m1), (f3, g3, s3, m3) = out
+    tol, ptol = TOL[precision]
+    ef = float((f1 - f3).abs().max() / f3.abs().max())
+    eg = float((g1 - g3).abs().max() / g3.abs().max())
+    es, em = abs(s1 - s3) / abs(s3), abs(m1 - m3) / abs(m3)
+    print(f"  rel f {ef:.2e} g {eg:.2e} sigma {es:.2e} M {em:.2e}", flush=True)
+    assert ef <= tol and eg <= tol and es <= ptol and em <= ptol
