@@ -68,7 +68,7 @@ typedef struct lbm3_ctx lbm3_ctx;
 
 /* Device workspace bytes for these parameters (0 when invalid): two
  * population buffers, the phi/mu/p fields and the momentum j between the two
- * collision kernels of the four-kernel form, reduction partials and two
+ * collision kernels of the three-launch form, reduction partials and two
  * int32 buffers of the Q2.29 phi sums of the fused FP32 step. */
 size_t lbm3_workspace_bytes(const lbm3_params* params);
 

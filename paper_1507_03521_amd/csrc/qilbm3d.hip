@@ -2,12 +2,13 @@
 // step (Yang & Guo, Sec. III, every term with three velocity components) for
 // gfx950, and its C ABI (include/qilbm3d.h).
 //
-// The step runs as four node-per-thread kernels, like the unfused
-// two-dimensional path: phi (the pulled g), mu (bulk part minus kappa times
-// the 19-point Laplacian of phi), the pressure (moments of the pulled f,
-// the stencils of phi and mu, force, velocity) with the collision of f,
-// which needs no grad p, and the collision of g (grad p from the pressure
-// field); or, in FP32, as one fused z-sweep kernel. Populations live in a pull
+// The step runs as three node-per-thread kernels over tiles
+// (qilbm3d_tile.hpp): phi (the pulled g); mu (bulk part minus kappa times the
+// 19-point Laplacian of phi), the pressure (moments of the pulled f, the
+// stencils of phi and mu, force, velocity) and the collision of f, which needs
+// no grad p; and the collision of g (grad p from the pressure field). Small
+// lattices take one or two launches, large FP32 ones one fused z-sweep
+// kernel. Populations live in a pull
 // layout: slot (i, x) holds the post-collision population i produced at x,
 // so the pre-collision value at x is slot (i, x - c_i), or slot (opp(i), x)
 // when x - c_i lies beyond a wall.
@@ -32,6 +33,7 @@ using qilbm::mu_bulk;
 using qilbm::recip;
 using qilbm::fmad;
 using qilbm::BUF_WORD3;
+using qilbm::CUS;
 using qilbm::buf_ld;
 using qilbm::buf_st;
 using qilbm::xcd_tile;
@@ -362,19 +364,38 @@ __device__ __forceinline__ void collide3(T f[19], T gg[19], const Node3<T>& m, c
   collide3_dirs(f, gg, n, q, CollK3<T>{}, c, T(1) - c.inv_tau_f, T(1) - c.inv_tau_g);
 }
 
-template <int I = 0, typename T>
-__device__ __forceinline__ void trt3_terms(T gg[19], T feq[19], T Fs[19], const CollNode3<T>& n,
+// f^eq, F_i and the collided g of direction I.
+template <int I, typename T>
+__device__ __forceinline__ void trt3_dir(T gg[19], T& feq, T& Fs, const CollNode3<T>& n,
+                                         const CollK3<T>& k, const Node3<T>& m, T src1, T ag) {
+  const T w = T(W(I));
+  T s, X, Y;
+  coll_dir3<I>(n, s, X, Y);
+  feq = w * fmad(m.rho * T(1.0 / 3.0), s, m.p);
+  Fs = w * (X + src1);
+  gg[I] = fmad(ag, gg[I], fmad(k.gy, Y, fmad(k.gs, s, k.g0)));
+}
+
+// The pair (I, I + 1) of opposite directions at a time, so that only one
+// pair's equilibria and sources are live.
+template <int I = 1, typename T>
+__device__ __forceinline__ void trt3_pairs(T f[19], T gg[19], const CollNode3<T>& n,
                                            const CollF3<T>& q, CollK3<T> k, const Node3<T>& m,
                                            const Coef<T>& c, T src1, T ag) {
   if constexpr (I < 19) {
-    if constexpr (I == 0 || I == 1 || I == 7) k = coll_k3<wclass3_of<I>()>(q, c);
-    const T w = T(W(I));
-    T s, X, Y;
-    coll_dir3<I>(n, s, X, Y);
-    feq[I] = w * fmad(m.rho * T(1.0 / 3.0), s, m.p);
-    Fs[I] = w * (X + src1);
-    gg[I] = fmad(ag, gg[I], fmad(k.gy, Y, fmad(k.gs, s, k.g0)));
-    trt3_terms<I + 1>(gg, feq, Fs, n, q, k, m, c, src1, ag);
+    if constexpr (I == 1 || I == 7) k = coll_k3<wclass3_of<I>()>(q, c);
+    constexpr int O = I + 1;
+    T ei, eo, Si, So;
+    trt3_dir<I>(gg, ei, Si, n, k, m, src1, ag);
+    trt3_dir<O>(gg, eo, So, n, k, m, src1, ag);
+    const T fp = T(0.5) * (f[I] + f[O]), fm = T(0.5) * (f[I] - f[O]);
+    const T ep = T(0.5) * (ei + eo), em = T(0.5) * (ei - eo);
+    const T sp = T(0.5) * (Si + So), sm = T(0.5) * (Si - So);
+    const T dpl = c.kf * sp - (fp - ep) * c.inv_tau_f;
+    const T dmi = c.km * sm - (fm - em) * c.inv_tau_m;
+    f[I] = f[I] + dpl + dmi;
+    f[O] = f[O] + dpl - dmi;
+    trt3_pairs<I + 2>(f, gg, n, q, k, m, c, src1, ag);
   }
 }
 
@@ -389,20 +410,11 @@ __device__ __forceinline__ void collide3_trt(T f[19], T gg[19], const Node3<T>& 
   const CollNode3<T> n = coll_node3(m, dp);
   const CollF3<T> q = coll_f3(m, c);
   const T src1 = -m.rho * c.gamma * m.D * T(1.0 / 3.0);
-  T feq[19], Fs[19];
-  trt3_terms(gg, feq, Fs, n, q, CollK3<T>{}, m, c, src1, T(1) - c.inv_tau_g);
-  f[0] = f[0] - (f[0] - feq[0]) * c.inv_tau_f + c.kf * Fs[0];
-#pragma unroll
-  for (int i = 1; i < 19; i += 2) {           // (i, i + 1) are opposite
-    const int o = i + 1;
-    const T fp = T(0.5) * (f[i] + f[o]), fm = T(0.5) * (f[i] - f[o]);
-    const T ep = T(0.5) * (feq[i] + feq[o]), em = T(0.5) * (feq[i] - feq[o]);
-    const T sp = T(0.5) * (Fs[i] + Fs[o]), sm = T(0.5) * (Fs[i] - Fs[o]);
-    const T dpl = c.kf * sp - (fp - ep) * c.inv_tau_f;
-    const T dmi = c.km * sm - (fm - em) * c.inv_tau_m;
-    f[i] = f[i] + dpl + dmi;
-    f[o] = f[o] + dpl - dmi;
-  }
+  const T ag = T(1) - c.inv_tau_g;
+  T e0, S0;
+  trt3_dir<0>(gg, e0, S0, n, coll_k3<0>(q, c), m, src1, ag);
+  f[0] = f[0] - (f[0] - e0) * c.inv_tau_f + c.kf * S0;
+  trt3_pairs(f, gg, n, q, CollK3<T>{}, m, c, src1, ag);
 }
 
 __host__ __device__ constexpr bool opposite_pairs_adjacent() {
@@ -611,33 +623,6 @@ __device__ __forceinline__ void stencil_r(const Planes<T, false>& F, const RowCt
   lp *= T(6);
 }
 
-template <int P, bool BIG>
-__global__ __launch_bounds__(256) void k3_phi(Pop3<P> in, typename PrecT<P>::T* __restrict__ phi,
-                                              Geom3 g, uint32_t nxc) {
-  using T = typename PrecT<P>::T;
-  const PopView<P, BIG> v(in);
-  const Planes<T, false> out(phi, g.Ns, 1);
-  for_rows<sizeof(T)>(g, nxc, [&](const RowCtx& R, const Lane& L) {
-    if constexpr (FixedG<P>::value) {
-      int32_t q = 0;
-#pragma unroll
-      for (int i = 0; i < 19; ++i) {
-        const Src s = pull_at(i, R, L);
-        q += v.g.ld(s.plane, s.row, s.vo);
-      }
-      out.st(0, R.rb[1][1], L.xo[1], T(q) * T(GQI));
-    } else {
-      T a = T(0);
-#pragma unroll
-      for (int i = 0; i < 19; ++i) {
-        const Src s = pull_at(i, R, L);
-        a += v.g.ld(s.plane, s.row, s.vo);
-      }
-      out.st(0, R.rb[1][1], L.xo[1], a);
-    }
-  });
-}
-
 // Pulled f of the lane's node and the node state from it and the phi, mu
 // fields.
 template <int P, bool BIG>
@@ -647,8 +632,7 @@ __device__ __forceinline__ void node_state_r(const PopView<P, BIG>& v,
                                              const RowCtx& R, const Lane& L,
                                              const Coef3<typename PrecT<P>::T>& k,
                                              typename PrecT<P>::T f[19],
-                                             Node3<typename PrecT<P>::T>& m,
-                                             typename PrecT<P>::T* jout = nullptr) {
+                                             Node3<typename PrecT<P>::T>& m) {
   using T = typename PrecT<P>::T;
 #pragma unroll
   for (int i = 0; i < 19; ++i) {
@@ -667,137 +651,12 @@ __device__ __forceinline__ void node_state_r(const PopView<P, BIG>& v,
   stencil_r<T>(ph, R, L, phi, gph[0], gph[1], gph[2], lphi);
   stencil_r<T>(mf, R, L, mu, gmu[0], gmu[1], gmu[2], lmu);
   macro3<T>(phi, mu, gph, gmu, lmu, S, j, k, m);
-  if (jout) {
-    jout[0] = j[0];
-    jout[1] = j[1];
-    jout[2] = j[2];
-  }
 }
 
 struct MomentOut3 {
   double *phi = nullptr, *rho = nullptr, *u[3] = {nullptr, nullptr, nullptr}, *p = nullptr,
          *mu = nullptr;
 };
-
-template <int P, bool BIG>
-__global__ __launch_bounds__(256) void k3_macro(Pop3<P> in, const typename PrecT<P>::T* __restrict__ phi,
-                                                const typename PrecT<P>::T* __restrict__ mu,
-                                                typename PrecT<P>::T* __restrict__ p,
-                                                MomentOut3 mo, Coef3<typename PrecT<P>::T> k,
-                                                Geom3 g, uint32_t nxc) {
-  using T = typename PrecT<P>::T;
-  const PopView<P, BIG> v(in);
-  const Planes<T, false> ph(phi, g.Ns, 1), mf(mu, g.Ns, 1), pf(p, g.Ns, 1);
-  for_rows<sizeof(T)>(g, nxc, [&](const RowCtx& R, const Lane& L) {
-    T f[19];
-    Node3<T> m;
-    node_state_r<P, BIG>(v, ph, mf, R, L, k, f, m);
-    if (p) pf.st(0, R.rb[1][1], L.xo[1], m.p);
-    const uint32_t n = R.rb[1][1] + L.x;
-    if (mo.phi) mo.phi[n] = double(m.phi);
-    if (mo.rho) mo.rho[n] = double(m.rho);
-    for (int a = 0; a < 3; ++a)
-      if (mo.u[a]) mo.u[a][n] = double(m.u[a]);
-    if (mo.p) mo.p[n] = double(m.p);
-    if (mo.mu) mo.mu[n] = double(m.mu);
-  });
-}
-
-// The collision in two kernels, so that each population set is pulled once:
-// f's collision needs no grad p, so k3_pf collides f where it forms the
-// pressure (and keeps j for k3_g); k3_g, after every p is written, pulls g
-// and collides it with grad p and with u and F re-formed from j and the
-// phi, mu stencils (the same arithmetic as in k3_pf; the pressure, which g
-// does not use, is left out).
-template <int P, bool BIG, bool TRT = false>
-__global__ __launch_bounds__(256) void k3_pf(Pop3<P> in, Pop3<P> out,
-                                             const typename PrecT<P>::T* __restrict__ phi,
-                                             const typename PrecT<P>::T* __restrict__ mu,
-                                             typename PrecT<P>::T* __restrict__ p,
-                                             typename PrecT<P>::T* __restrict__ jx,
-                                             typename PrecT<P>::T* __restrict__ jy,
-                                             typename PrecT<P>::T* __restrict__ jz,
-                                             Coef3<typename PrecT<P>::T> k, Geom3 g, uint32_t nxc) {
-  using T = typename PrecT<P>::T;
-  const PopView<P, BIG> v(in), w(out);
-  const Planes<T, false> ph(phi, g.Ns, 1), mf(mu, g.Ns, 1), pf(p, g.Ns, 1);
-  const Planes<T, false> jf[3] = {{jx, g.Ns, 1}, {jy, g.Ns, 1}, {jz, g.Ns, 1}};
-  for_rows<sizeof(T)>(g, nxc, [&](const RowCtx& R, const Lane& L) {
-    T f[19], j[3];
-    Node3<T> m;
-    node_state_r<P, BIG>(v, ph, mf, R, L, k, f, m, j);
-    const uint32_t row = R.rb[1][1], vo = L.xo[1];
-    pf.st(0, row, vo, m.p);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) jf[a].st(0, row, vo, j[a]);
-    const T dp0[3] = {T(0), T(0), T(0)};
-    T gd[19];
-#pragma unroll
-    for (int i = 0; i < 19; ++i) gd[i] = T(0);
-    if constexpr (TRT) collide3_trt<T>(f, gd, m, dp0, k.c);
-    else collide3<T>(f, gd, m, dp0, k.c);
-#pragma unroll
-    for (int i = 0; i < 19; ++i) w.f.st(i, row, vo, f[i]);
-  });
-}
-
-template <int P, bool BIG, bool TRT = false>
-__global__ __launch_bounds__(256) void k3_g(Pop3<P> in, Pop3<P> out,
-                                            const typename PrecT<P>::T* __restrict__ phi,
-                                            const typename PrecT<P>::T* __restrict__ mu,
-                                            const typename PrecT<P>::T* __restrict__ p,
-                                            const typename PrecT<P>::T* __restrict__ jx,
-                                            const typename PrecT<P>::T* __restrict__ jy,
-                                            const typename PrecT<P>::T* __restrict__ jz,
-                                            Coef3<typename PrecT<P>::T> k, Geom3 g, uint32_t nxc) {
-  using T = typename PrecT<P>::T;
-  const PopView<P, BIG> v(in), w(out);
-  const Planes<T, false> ph(phi, g.Ns, 1), mf(mu, g.Ns, 1), pf(p, g.Ns, 1);
-  const Planes<T, false> jf[3] = {{jx, g.Ns, 1}, {jy, g.Ns, 1}, {jz, g.Ns, 1}};
-  for_rows<sizeof(T)>(g, nxc, [&](const RowCtx& R, const Lane& L) {
-    T gg[19];
-    int32_t q = 0;
-#pragma unroll
-    for (int i = 0; i < 19; ++i) {
-      const Src s = pull_at(i, R, L);
-      if constexpr (FixedG<P>::value) {
-        const int32_t word = v.g.ld(s.plane, s.row, s.vo);
-        q += word;
-        gg[i] = float(word) * GQI;
-      } else {
-        gg[i] = v.g.ld(s.plane, s.row, s.vo);
-      }
-    }
-    const uint32_t row = R.rb[1][1], vo = L.xo[1];
-    const T j[3] = {jf[0].ld(0, row, vo), jf[1].ld(0, row, vo), jf[2].ld(0, row, vo)};
-    T phi, mu, gph[3], gmu[3], lphi, lmu;
-    stencil_r<T>(ph, R, L, phi, gph[0], gph[1], gph[2], lphi);
-    stencil_r<T>(mf, R, L, mu, gmu[0], gmu[1], gmu[2], lmu);
-    Node3<T> m;
-    macro3<T>(phi, mu, gph, gmu, lmu, T(0), j, k, m);
-    T p0, dp[3], lapp;
-    stencil_r<T>(pf, R, L, p0, dp[0], dp[1], dp[2], lapp);
-    T fd[19];
-#pragma unroll
-    for (int i = 0; i < 19; ++i) fd[i] = T(0);
-    if constexpr (TRT) collide3_trt<T>(fd, gg, m, dp, k.c);
-    else collide3<T>(fd, gg, m, dp, k.c);
-    if constexpr (FixedG<P>::value) {
-      // g_0 closes the node's Q2.29 sum at the pulled total q
-      int32_t rest = 0;
-#pragma unroll
-      for (int i = 1; i < 19; ++i) {
-        const int32_t word = __float2int_rn(gg[i] * GQ);
-        rest += word;
-        w.g.st(i, row, vo, word);
-      }
-      w.g.st(0, row, vo, q - rest);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 19; ++i) w.g.st(i, row, vo, gg[i]);
-    }
-  });
-}
 
 // Q2.29 sum of the pulled g words of every node (the order parameter the
 // fused FP32 step reads in its stage A).
@@ -831,14 +690,14 @@ __global__ __launch_bounds__(256) void k3_phiq(Pop3<P_F32> in, int32_t* __restri
 // is pulled from HBM once (f by C, g by D) and written once. Halo nodes and
 // the 3 planes of warm-up at each segment end are
 // recomputed by the neighbouring workgroups. Results equal those of the
-// four-kernel path up to the rounding order of contracted multiply-adds.
-// (The four kernels split the two collisions the same way.)
+// node-per-thread path up to the rounding order of contracted multiply-adds.
+// (Its kernels split the two collisions the same way.)
 // Used for FP32 only, with stage A reading phi from the Q2.29 words that the
 // previous step scattered (PHIQ below): pulling g there over the halo made
 // the kernel read 453 B per node (those re-reads miss L2), against 252 with
 // the scattered phi. In FP64 (no integer g; LDS rings for one 512-lane
 // workgroup per CU, barrier-bound) the fused form was a quarter slower than
-// the four kernels.
+// the node-per-thread kernels.
 namespace fz {
 // 64 x 16 columns on 512 lanes (two core nodes per lane): 79 KB of LDS,
 // one workgroup (eight waves) per CU, 3 % faster than 64 x 8 columns on 256
@@ -975,7 +834,7 @@ __device__ __forceinline__ void lds_stencil(const T* pm, const T* p0, const T* p
 }
 
 // mu = mu_bulk(phi) - kappa lap(phi) (Sec. II, the chemical potential) of a
-// 64 x 4 column tile over a segment of MZ_ZS planes: the phi planes of the
+// 64 x 4 column tile over a segment of zs planes: the phi planes of the
 // tile and the ring of nodes around it go through a ring of four LDS planes,
 // so each phi value is read from memory about once instead of once per
 // stencil neighbour. Beyond a wall the mirrored ghost plane is the wall plane
@@ -988,14 +847,14 @@ __host__ __device__ inline int mu_tiles_xy(const Geom3& g) {
 
 template <typename T>
 __global__ __launch_bounds__(256) void k3_mu(const T* __restrict__ phi, T* __restrict__ mu,
-                                             Coef3<T> k, Geom3 g) {
+                                             Coef3<T> k, Geom3 g, int zs) {
   __shared__ T ring[4][MZ_A];
   const int ntx = (g.nx + MZ_TX - 1) / MZ_TX, nxy = mu_tiles_xy(g);
   const int b = xcd_tile((int)blockIdx.x, (int)gridDim.x);
   const int seg = b / nxy, txy = b - seg * nxy;
   const int ty = txy / ntx, tx = txy - ty * ntx;
   const int x0 = tx * MZ_TX, y0 = ty * MZ_TY;
-  const int z0 = seg * MZ_ZS, z1 = min(g.nz, z0 + MZ_ZS);
+  const int z0 = seg * zs, z1 = min(g.nz, z0 + zs);
   const int t = threadIdx.x, lx = t & 63, ly = t >> 6;
   const int x = x0 + lx, y = y0 + ly;
   const uint32_t nx = (uint32_t)g.nx, ny = (uint32_t)g.ny;
@@ -1453,6 +1312,8 @@ __global__ __launch_bounds__(256) void k3_sum5(const double* __restrict__ part, 
 
 }  // namespace qilbm3
 
+#include "qilbm3d_tile.hpp"
+
 // ====================================================================== C ABI
 using namespace qilbm3;
 
@@ -1577,74 +1438,132 @@ bool big3(const Geom3& g) {
 
 lbm_status st(hipError_t e) { return e == hipSuccess ? LBM_OK : LBM_EDEVICE; }
 
+// Runs FN<BIG, TX, TY, TZ>() for the lattice's tile shape: 32 nodes wide, or 16
+// where 32 would leave a quarter or more of the lanes without a node (nx up to
+// 16, 33 to 48). Whole rows of 32 load fewer lines twice: 256^3 in FP64 3.06
+// ms a step against 3.15 in 16 x 4 x 4, FP32 (LBM_FLAG_UNFUSED) 1.54 against
+// 1.86; 48^3 33 us against 26.
+template <int P, typename Fn>
+hipError_t with_tile(const Geom3& g, Fn&& fn) {
+  const bool narrow = (g.nx + 15) / 16 * 16 * 4 <= (g.nx + 31) / 32 * 32 * 3;
+  if (big3<P>(g)) {
+    if (narrow) fn(Tile3<true, 16, 4, 4>{});
+    else fn(Tile3<true, 32, 4, 4>{});
+  } else {
+    if (narrow) fn(Tile3<false, 16, 4, 4>{});
+    else fn(Tile3<false, 32, 4, 4>{});
+  }
+  return hipGetLastError();
+}
+
+// Planes of the context's fields.
+template <typename T>
+struct Fields3 {
+  T *phi, *mu, *p, *j[3];
+  explicit Fields3(const lbm3_ctx* c) {
+    T** const out[6] = {&phi, &mu, &p, &j[0], &j[1], &j[2]};
+    for (int i = 0; i < 6; ++i) *out[i] = (T*)(c->fields + i * c->geom.Ns * 8);
+  }
+};
+
+template <int P, typename TL>
+void launch_tile_phi(lbm3_ctx* c, TL) {
+  const Geom3& g = c->geom;
+  const Pop3<P> in{c->pop[c->cur], g.Ns};
+  hipLaunchKernelGGL((k3_tile_phi<P, TL::big, TL::x, TL::y, TL::z>),
+                     dim3((unsigned)TL::count(g)), dim3(TL::n), 0, c->stream, in,
+                     Fields3<typename PrecT<P>::T>(c).phi, g);
+}
+
+template <int P>
+hipError_t phi_p(lbm3_ctx* c) {
+  return with_tile<P>(c->geom, [&](auto tl) { launch_tile_phi<P>(c, tl); });
+}
+
+// phi and mu fields of the current state.
 template <int P>
 hipError_t fields_p(lbm3_ctx* c) {
   using T = typename PrecT<P>::T;
   const Geom3& g = c->geom;
-  Pop3<P> in{c->pop[c->cur], g.Ns};
-  T* phi = (T*)c->fields;
-  T* mu = (T*)(c->fields + g.Ns * 8);
-  const uint32_t nxc = chunks_x(g);
-  if (big3<P>(g))
-    hipLaunchKernelGGL((k3_phi<P, true>), dim3(row_grid(g)), dim3(256), 0, c->stream, in, phi, g,
-                       nxc);
-  else
-    hipLaunchKernelGGL((k3_phi<P, false>), dim3(row_grid(g)), dim3(256), 0, c->stream, in, phi, g,
-                       nxc);
-  const int64_t mu_blocks = (int64_t)mu_tiles_xy(g) * ((g.nz + MZ_ZS - 1) / MZ_ZS);
+  const Fields3<T> fl(c);
+  if (phi_p<P>(c) != hipSuccess) return hipErrorLaunchFailure;
+  // segments of 32 planes, shorter on a lattice with too few columns for one
+  // workgroup per CU (32^3: eight workgroups 36 us, 64 of four planes 5 us)
+  int zs = MZ_ZS;
+  while (zs > 4 && (int64_t)mu_tiles_xy(g) * ((g.nz + zs - 1) / zs) < CUS) zs /= 2;
+  const int64_t mu_blocks = (int64_t)mu_tiles_xy(g) * ((g.nz + zs - 1) / zs);
   hipLaunchKernelGGL(k3_mu<T>, dim3((unsigned)mu_blocks), dim3(256), 0, c->stream,
-                     (const T*)phi, mu, coef3<T>(c), g);
+                     (const T*)fl.phi, fl.mu, coef3<T>(c), g, zs);
   return hipGetLastError();
 }
 
-template <int P, bool BIG>
-void launch_macro(lbm3_ctx* c, typename PrecT<P>::T* p, const MomentOut3& mo) {
+// One step in three launches.
+template <int P>
+hipError_t step_tiles(lbm3_ctx* c) {
   using T = typename PrecT<P>::T;
   const Geom3& g = c->geom;
-  Pop3<P> in{c->pop[c->cur], g.Ns};
-  hipLaunchKernelGGL((k3_macro<P, BIG>), dim3(row_grid(g)), dim3(256), 0, c->stream, in,
-                     (const T*)c->fields, (const T*)(c->fields + g.Ns * 8), p, mo, coef3<T>(c), g,
-                     chunks_x(g));
+  const Pop3<P> in{c->pop[c->cur], g.Ns}, out{c->pop[c->cur ^ 1], g.Ns};
+  const Fields3<T> fl(c);
+  const Coef3<T> k = coef3<T>(c);
+  return with_tile<P>(g, [&](auto tl) {
+    using TL = decltype(tl);
+    const dim3 grid((unsigned)TL::count(g)), block(TL::n);
+    launch_tile_phi<P>(c, tl);
+    if (c->prm.trt_magic > 0.0)
+      hipLaunchKernelGGL((k3_tile_f<P, TL::big, true, TL::x, TL::y, TL::z>), grid, block, 0,
+                         c->stream, in, out, (const T*)fl.phi, fl.mu, fl.p, fl.j[0], fl.j[1],
+                         fl.j[2], k, g);
+    else
+      hipLaunchKernelGGL((k3_tile_f<P, TL::big, false, TL::x, TL::y, TL::z>), grid, block, 0,
+                         c->stream, in, out, (const T*)fl.phi, fl.mu, fl.p, fl.j[0], fl.j[1],
+                         fl.j[2], k, g);
+    hipLaunchKernelGGL((k3_tile_g<P, TL::big, TL::x, TL::y, TL::z>), grid, block, 0, c->stream,
+                       in, out, (const T*)fl.phi, (const T*)fl.mu, (const T*)fl.p,
+                       (const T*)fl.j[0], (const T*)fl.j[1], (const T*)fl.j[2], k, g);
+  });
 }
 
-template <int P, bool BIG>
-void launch_collide(lbm3_ctx* c) {
+// One step of a small lattice: k3_tile_step, with phi pulled over the halo or
+// read after k3_tile_phi.
+template <int P, bool PULL, int TX, int TY, int TZ, int NT>
+hipError_t step_small(lbm3_ctx* c) {
   using T = typename PrecT<P>::T;
   const Geom3& g = c->geom;
-  Pop3<P> in{c->pop[c->cur], g.Ns}, out{c->pop[c->cur ^ 1], g.Ns};
-  T* phi = (T*)c->fields;
-  T* mu = (T*)(c->fields + g.Ns * 8);
-  T* p = (T*)(c->fields + 2 * g.Ns * 8);
-  T* jx = (T*)(c->fields + 3 * g.Ns * 8);
-  T* jy = (T*)(c->fields + 4 * g.Ns * 8);
-  T* jz = (T*)(c->fields + 5 * g.Ns * 8);
-  if (c->prm.trt_magic > 0.0) {
-    hipLaunchKernelGGL((k3_pf<P, BIG, true>), dim3(row_grid(g)), dim3(256), 0, c->stream, in, out,
-                       (const T*)phi, (const T*)mu, p, jx, jy, jz, coef3<T>(c), g, chunks_x(g));
-    hipLaunchKernelGGL((k3_g<P, BIG, true>), dim3(row_grid(g)), dim3(256), 0, c->stream, in, out,
-                       (const T*)phi, (const T*)mu, (const T*)p, (const T*)jx, (const T*)jy,
-                       (const T*)jz, coef3<T>(c), g, chunks_x(g));
-  } else {
-    hipLaunchKernelGGL((k3_pf<P, BIG, false>), dim3(row_grid(g)), dim3(256), 0, c->stream, in,
-                       out, (const T*)phi, (const T*)mu, p, jx, jy, jz, coef3<T>(c), g,
-                       chunks_x(g));
-    hipLaunchKernelGGL((k3_g<P, BIG, false>), dim3(row_grid(g)), dim3(256), 0, c->stream, in,
-                       out, (const T*)phi, (const T*)mu, (const T*)p, (const T*)jx,
-                       (const T*)jy, (const T*)jz, coef3<T>(c), g, chunks_x(g));
-  }
+  const Pop3<P> in{c->pop[c->cur], g.Ns}, out{c->pop[c->cur ^ 1], g.Ns};
+  const T* const phi = Fields3<T>(c).phi;
+  const dim3 grid((unsigned)tile_count<TX, TY, TZ>(g)), block(NT);
+  if constexpr (!PULL) launch_tile_phi<P>(c, Tile3<false, 16, 4, 4>{});
+  if (c->prm.trt_magic > 0.0)
+    hipLaunchKernelGGL((k3_tile_step<P, false, true, PULL, TX, TY, TZ, NT>), grid, block, 0,
+                       c->stream, in, out, phi, coef3<T>(c), g);
+  else
+    hipLaunchKernelGGL((k3_tile_step<P, false, false, PULL, TX, TY, TZ, NT>), grid, block, 0,
+                       c->stream, in, out, phi, coef3<T>(c), g);
+  return hipGetLastError();
 }
 
-// workgroups of the kernel that will run resident on the whole GPU at once
-template <int P, bool TRT>
+// While one round of workgroups (FP32: two) covers a lattice in the tiles of
+// k3_tile_step, it is the faster: FP64 16 x 32 x 32 12.4 us a step in one
+// launch, 13.1 in two, 16.1 in three; 32^3 16.5, 14.2, 16.6; 40^3 28, 24, 22.
+// FP32 40^3 19.8, 16.4, 18.1; 48^3 34, 25, 20.
+template <int P>
+bool small_one(const Geom3& g) {
+  return tile_count<4, 4, 4>(g) <= CUS;
+}
+template <int P>
+bool small_two(const Geom3& g) {
+  return tile_count<8, 4, 4>(g) <= (P == P_F32 ? 2 * CUS : CUS);
+}
+
+// Compute units of the current device: the z-sweep kernel runs one workgroup
+// on each. Two fit the TRT variant's 127 registers, and are slower (256^3 1435
+// us a step against 1375): more segments, each with its warm-up planes.
 int fused_resident3() {
-  int dev = 0, cus = 0, per_cu = 0;
+  int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k3_fused<P, false, true, TRT>,
-                                                   FzThreads<P>::value, 0) != hipSuccess)
-    return 0;
-  return cus * (per_cu > 0 ? per_cu : 1);
+  return cus;
 }
 
 // Tiles of TX x TY columns times z-segments, one round of workgroups.
@@ -1661,13 +1580,9 @@ Fz3Shape fused_shape3(const Geom3& g, int resident) {
 }
 
 template <int P>
-lbm_status step_fused_p(lbm3_ctx* c, int64_t n) {
+lbm_status step_fused_p(lbm3_ctx* c, int64_t n, const Fz3Shape& sh) {
   using T = typename PrecT<P>::T;
   const Geom3& g = c->geom;
-  if (c->resident == 0)
-    c->resident = c->prm.trt_magic > 0.0 ? fused_resident3<P, true>() : fused_resident3<P, false>();
-  if (c->resident <= 0) return LBM_EDEVICE;
-  const Fz3Shape sh = fused_shape3(g, c->resident);
   const unsigned nblk = (unsigned)(sh.ntx * sh.nty * sh.nseg);
   const Coef3<T> k = coef3<T>(c);
   const bool big = big3<P>(g);
@@ -1711,19 +1626,31 @@ lbm_status step_fused_p(lbm3_ctx* c, int64_t n) {
 
 template <int P>
 lbm_status step_p(lbm3_ctx* c, int64_t n) {
-  using T = typename PrecT<P>::T;
   const Geom3& g = c->geom;
-  if constexpr (P == P_F32)
-    if (!(c->prm.flags & LBM_FLAG_UNFUSED)) return step_fused_p<P>(c, n);
+  const bool one = small_one<P>(g), two = small_two<P>(g);
+  const bool unfused = c->prm.flags & LBM_FLAG_UNFUSED;
+  if constexpr (P == P_F32) {
+    // The z-sweep takes some 13 us a plane of its segments and six more of
+    // warm-up (whatever the lattice, which only sets the segments' length),
+    // the three launches 93 us per million nodes. Measured, z-sweep and
+    // tiles: 128^3 183 and 194 us, 256 x 256 x 64 353 and 398, 256^3 1290
+    // and 1540; 128 x 128 x 64 103 and 96, 96^3 103 and 77, 65 x 130 x 130
+    // 178 and 127, 20 x 250 x 250 264 and 133.
+    if (!unfused && !one && !two) {
+      if (c->resident == 0) c->resident = fused_resident3();
+      if (c->resident <= 0) return LBM_EDEVICE;
+      const Fz3Shape sh = fused_shape3(g, c->resident);
+      if (g.N > (int64_t)140000 * (sh.seg + 6)) return step_fused_p<P>(c, n, sh);
+    }
+  }
   c->phiq_ok = false;
-  const bool big = big3<P>(g);
   for (int64_t s = 0; s < n; ++s) {
-    if (fields_p<P>(c) != hipSuccess) return LBM_EDEVICE;
-    if (big)
-      launch_collide<P, true>(c);
-    else
-      launch_collide<P, false>(c);
-    if (hipGetLastError() != hipSuccess) return LBM_EDEVICE;
+    hipError_t e;
+    if (unfused) e = step_tiles<P>(c);
+    else if (one) e = step_small<P, true, 4, 4, 4, 256>(c);
+    else if (two) e = step_small<P, false, 8, 4, 4, 384>(c);
+    else e = step_tiles<P>(c);
+    if (e != hipSuccess) return LBM_EDEVICE;
     c->cur ^= 1;
     c->t += 1;
   }
@@ -1732,12 +1659,16 @@ lbm_status step_p(lbm3_ctx* c, int64_t n) {
 
 template <int P>
 lbm_status moments_p(lbm3_ctx* c, const MomentOut3& mo) {
-  if (fields_p<P>(c) != hipSuccess) return LBM_EDEVICE;
-  if (big3<P>(c->geom))
-    launch_macro<P, true>(c, nullptr, mo);
-  else
-    launch_macro<P, false>(c, nullptr, mo);
-  return st(hipGetLastError());
+  using T = typename PrecT<P>::T;
+  const Geom3& g = c->geom;
+  const Pop3<P> in{c->pop[c->cur], g.Ns};
+  return st(with_tile<P>(g, [&](auto tl) {
+    using TL = decltype(tl);
+    launch_tile_phi<P>(c, tl);
+    hipLaunchKernelGGL((k3_tile_macro<P, TL::big, TL::x, TL::y, TL::z>),
+                       dim3((unsigned)TL::count(g)), dim3(TL::n), 0, c->stream, in,
+                       (const T*)Fields3<T>(c).phi, mo, coef3<T>(c), g);
+  }));
 }
 
 template <int P>

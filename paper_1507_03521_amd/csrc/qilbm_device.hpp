@@ -266,6 +266,8 @@ __device__ __forceinline__ void buf_st(S v, __amdgpu_buffer_rsrc_t r, uint32_t v
   }
 }
 
+constexpr int CUS = 256;    // compute units: a grid of at most as many workgroups is one round
+
 // Tiles handed out so that blocks that the hardware places on one XCD
 // (consecutive blocks round-robin over 8 XCDs) get consecutive tiles, i.e.
 // neighbouring tiles share that XCD's L2.

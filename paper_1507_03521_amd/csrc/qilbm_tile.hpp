@@ -67,7 +67,6 @@ __device__ __forceinline__ void tile3x3(const T* a, int e, bool lo, bool hi, T v
   }
 }
 
-constexpr int CUS = 256;    // compute units: a grid of at most as many tiles is one round
 
 // Tiles of tx x ty nodes that cover the lattice.
 inline int tiles(const Geom& g, int tx, int ty) {
