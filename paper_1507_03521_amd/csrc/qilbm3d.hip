@@ -37,6 +37,9 @@ using qilbm::CUS;
 using qilbm::buf_ld;
 using qilbm::buf_st;
 using qilbm::xcd_tile;
+using qilbm::ST_BACK;
+using qilbm::ST_STREAM;
+using qilbm::ST_THROUGH;
 
 // ------------------------------------------------------------------ lattice
 // D3Q19 in the canonical order of the header: rest; the six axis vectors;
@@ -570,8 +573,9 @@ struct Planes {
   __device__ __forceinline__ S ldb(int plane, uint32_t sb, uint32_t vb) const {
     return buf_ld<S>(rsrc(plane), vb, (BIG ? 0u : (uint32_t)plane * pb) + sb);
   }
+  template <int POL = qilbm::ST_BACK>
   __device__ __forceinline__ void stb(int plane, uint32_t sb, uint32_t vb, S v) const {
-    buf_st<S>(v, rsrc(plane), vb, (BIG ? 0u : (uint32_t)plane * pb) + sb);
+    buf_st<S, POL>(v, rsrc(plane), vb, (BIG ? 0u : (uint32_t)plane * pb) + sb);
   }
 };
 
@@ -895,7 +899,7 @@ __global__ __launch_bounds__(256) void k3_mu(const T* __restrict__ phi, T* __res
 // exactly. Every target (core tile plus a one-node ring) accumulates in LDS
 // (three planes, flushed with one atomic add per node once a plane has all
 // its sources from this tile).
-template <int P, bool BIG, bool PHIQ = false, bool TRT = false>
+template <int P, bool BIG, bool PHIQ, bool TRT, int POL>
 __global__ __launch_bounds__(FzThreads<P>::value) void k3_fused(Pop3<P> in, Pop3<P> out,
                                                                 Coef3<typename PrecT<P>::T> k,
                                                                 Geom3 g, Fz3Shape sh,
@@ -1078,7 +1082,7 @@ __global__ __launch_bounds__(FzThreads<P>::value) void k3_fused(Pop3<P> in, Pop3
           else collide3<T>(f, gd, m, dp0, k.c);
           const uint32_t sb = Z.zo[1], vb = q.yo[1] + q.xo[1];
 #pragma unroll
-          for (int i = 0; i < 19; ++i) w.f.stb(i, sb, vb, f[i]);
+          for (int i = 0; i < 19; ++i) w.f.template stb<POL>(i, sb, vb, f[i]);
         }
       }
       constexpr int RING = RC::A - TX * TY;    // 2 (TX + 2) + 2 TY
@@ -1161,7 +1165,7 @@ __global__ __launch_bounds__(FzThreads<P>::value) void k3_fused(Pop3<P> in, Pop3
           for (int i = 1; i < 19; ++i) {
             const int32_t word = __float2int_rn(gg[i] * GQ);
             rest += word;
-            w.g.stb(i, sb, vb, word);
+            w.g.template stb<POL>(i, sb, vb, word);
             if constexpr (PHIQ) {
               // the word streams to (X, Y, zd) + c_i, or back to this node
               // (as the opposite population) beyond a wall
@@ -1172,11 +1176,11 @@ __global__ __launch_bounds__(FzThreads<P>::value) void k3_fused(Pop3<P> in, Pop3
                 atomicAdd(&L.acc[(zt - vbase) % 3][er + CY(i) * RC::W + CX(i)], word);
             }
           }
-          w.g.stb(0, sb, vb, qs - rest);
+          w.g.template stb<POL>(0, sb, vb, qs - rest);
           if constexpr (PHIQ) atomicAdd(&L.acc[(zd - vbase) % 3][er], qs - rest);
         } else {
 #pragma unroll
-          for (int i = 0; i < 19; ++i) w.g.stb(i, sb, vb, gg[i]);
+          for (int i = 0; i < 19; ++i) w.g.template stb<POL>(i, sb, vb, gg[i]);
         }
       }
     }
@@ -1438,7 +1442,21 @@ bool big3(const Geom3& g) {
 
 lbm_status st(hipError_t e) { return e == hipSuccess ? LBM_OK : LBM_EDEVICE; }
 
-// Runs FN<BIG, TX, TY, TZ>() for the lattice's tile shape: 32 nodes wide, or 16
+// How the collisions store. Rows of whole 128-byte lines: written through
+// while both population buffers stay near the 256 MB Infinity Cache (what a
+// kernel leaves dirty in L2 is written back when it ends, with nothing to
+// overlap that: FP64 64^3 44.3 us a step, 41.1 through, FP32 28.4, 26.4),
+// beyond as a stream (FP64 128^3 400, 366, FP32 185, 175; 256^3 3050, 2956 and
+// 1292, 1238). Other rows share lines between tiles, which both policies
+// write in parts (FP64 100^3 209, 233 and 247).
+template <int P>
+int store_policy(const Geom3& g) {
+  const int ws = sizeof(typename PrecT<P>::T);
+  if ((int64_t)g.nx * ws % 128 != 0) return ST_BACK;
+  return 2 * pop3_bytes(P, g.Ns) <= (int64_t)320 << 20 ? ST_THROUGH : ST_STREAM;
+}
+
+// Runs fn(Tile3<BIG, TX, TY, TZ>{}) for the lattice's tile shape: 32 nodes wide, or 16
 // where 32 would leave a quarter or more of the lanes without a node (nx up to
 // 16, 33 to 48). Whole rows of 32 load fewer lines twice: 256^3 in FP64 3.06
 // ms a step against 3.15 in 16 x 4 x 4, FP32 (LBM_FLAG_UNFUSED) 1.54 against
@@ -1497,9 +1515,9 @@ hipError_t fields_p(lbm3_ctx* c) {
   return hipGetLastError();
 }
 
-// One step in three launches.
-template <int P>
-hipError_t step_tiles(lbm3_ctx* c) {
+// One step in three launches, whose collisions store with policy POL.
+template <int P, int POL>
+hipError_t step_tiles_pol(lbm3_ctx* c) {
   using T = typename PrecT<P>::T;
   const Geom3& g = c->geom;
   const Pop3<P> in{c->pop[c->cur], g.Ns}, out{c->pop[c->cur ^ 1], g.Ns};
@@ -1510,17 +1528,26 @@ hipError_t step_tiles(lbm3_ctx* c) {
     const dim3 grid((unsigned)TL::count(g)), block(TL::n);
     launch_tile_phi<P>(c, tl);
     if (c->prm.trt_magic > 0.0)
-      hipLaunchKernelGGL((k3_tile_f<P, TL::big, true, TL::x, TL::y, TL::z>), grid, block, 0,
+      hipLaunchKernelGGL((k3_tile_f<P, TL::big, true, POL, TL::x, TL::y, TL::z>), grid, block, 0,
                          c->stream, in, out, (const T*)fl.phi, fl.mu, fl.p, fl.j[0], fl.j[1],
                          fl.j[2], k, g);
     else
-      hipLaunchKernelGGL((k3_tile_f<P, TL::big, false, TL::x, TL::y, TL::z>), grid, block, 0,
+      hipLaunchKernelGGL((k3_tile_f<P, TL::big, false, POL, TL::x, TL::y, TL::z>), grid, block, 0,
                          c->stream, in, out, (const T*)fl.phi, fl.mu, fl.p, fl.j[0], fl.j[1],
                          fl.j[2], k, g);
-    hipLaunchKernelGGL((k3_tile_g<P, TL::big, TL::x, TL::y, TL::z>), grid, block, 0, c->stream,
-                       in, out, (const T*)fl.phi, (const T*)fl.mu, (const T*)fl.p,
+    hipLaunchKernelGGL((k3_tile_g<P, TL::big, POL, TL::x, TL::y, TL::z>), grid, block, 0,
+                       c->stream, in, out, (const T*)fl.phi, (const T*)fl.mu, (const T*)fl.p,
                        (const T*)fl.j[0], (const T*)fl.j[1], (const T*)fl.j[2], k, g);
   });
+}
+
+template <int P>
+hipError_t step_tiles(lbm3_ctx* c) {
+  switch (store_policy<P>(c->geom)) {
+    case ST_THROUGH: return step_tiles_pol<P, ST_THROUGH>(c);
+    case ST_STREAM: return step_tiles_pol<P, ST_STREAM>(c);
+    default: return step_tiles_pol<P, ST_BACK>(c);
+  }
 }
 
 // One step of a small lattice: k3_tile_step, with phi pulled over the halo or
@@ -1579,14 +1606,27 @@ Fz3Shape fused_shape3(const Geom3& g, int resident) {
   return sh;
 }
 
+template <int P, bool BIG>
+void launch_fused3(lbm3_ctx* c, const Pop3<P>& in, const Pop3<P>& out,
+                   const Coef3<typename PrecT<P>::T>& k, const Fz3Shape& sh, const int32_t* qin,
+                   int32_t* qout) {
+  const dim3 grid((unsigned)(sh.ntx * sh.nty * sh.nseg)), block(FzThreads<P>::value);
+  const auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, c->stream, in, out, k, c->geom, sh, qin, qout);
+  };
+  const bool trt = c->prm.trt_magic > 0.0, stream = store_policy<P>(c->geom) == ST_STREAM;
+  if (trt && stream) go(k3_fused<P, BIG, true, true, ST_STREAM>);
+  else if (trt) go(k3_fused<P, BIG, true, true, ST_BACK>);
+  else if (stream) go(k3_fused<P, BIG, true, false, ST_STREAM>);
+  else go(k3_fused<P, BIG, true, false, ST_BACK>);
+}
+
 template <int P>
 lbm_status step_fused_p(lbm3_ctx* c, int64_t n, const Fz3Shape& sh) {
   using T = typename PrecT<P>::T;
   const Geom3& g = c->geom;
-  const unsigned nblk = (unsigned)(sh.ntx * sh.nty * sh.nseg);
   const Coef3<T> k = coef3<T>(c);
   const bool big = big3<P>(g);
-  const bool trt = c->prm.trt_magic > 0.0;
   if (n > 0 && !c->phiq_ok) {
     Pop3<P_F32> in{c->pop[c->cur], g.Ns};
     if (big)
@@ -1603,19 +1643,8 @@ lbm_status step_fused_p(lbm3_ctx* c, int64_t n, const Fz3Shape& sh) {
     int32_t* qin = c->phiq[c->qcur];
     int32_t* qout = c->phiq[c->qcur ^ 1];
     if (qilbm::launch_zero(qout, (size_t)g.Ns * 4, c->stream) != hipSuccess) return LBM_EDEVICE;
-    const dim3 grid(nblk), block(FzThreads<P>::value);
-    if (big && trt)
-      hipLaunchKernelGGL((k3_fused<P, true, true, true>), grid, block, 0, c->stream, in, out, k,
-                         g, sh, (const int32_t*)qin, qout);
-    else if (big)
-      hipLaunchKernelGGL((k3_fused<P, true, true, false>), grid, block, 0, c->stream, in, out, k,
-                         g, sh, (const int32_t*)qin, qout);
-    else if (trt)
-      hipLaunchKernelGGL((k3_fused<P, false, true, true>), grid, block, 0, c->stream, in, out, k,
-                         g, sh, (const int32_t*)qin, qout);
-    else
-      hipLaunchKernelGGL((k3_fused<P, false, true, false>), grid, block, 0, c->stream, in, out, k,
-                         g, sh, (const int32_t*)qin, qout);
+    if (big) launch_fused3<P, true>(c, in, out, k, sh, qin, qout);
+    else launch_fused3<P, false>(c, in, out, k, sh, qin, qout);
     if (hipGetLastError() != hipSuccess) return LBM_EDEVICE;
     c->cur ^= 1;
     c->qcur ^= 1;

@@ -191,7 +191,7 @@ __device__ __forceinline__ int32_t g_values(const GW gw[19], T gg[19]) {
 
 // Stores a node's collided g; in FP32 g_0 closes the node's Q2.29 sum at the
 // pulled total q.
-template <int P, bool BIG, typename T>
+template <int POL, int P, bool BIG, typename T>
 __device__ __forceinline__ void g_store(const PopView<P, BIG>& w, uint32_t n, const T gg[19],
                                         int32_t q) {
   if constexpr (FixedG<P>::value) {
@@ -200,13 +200,19 @@ __device__ __forceinline__ void g_store(const PopView<P, BIG>& w, uint32_t n, co
     for (int i = 1; i < 19; ++i) {
       const int32_t word = __float2int_rn(gg[i] * GQ);
       rest += word;
-      w.g.stb(i, 0, n, word);
+      w.g.template stb<POL>(i, 0, n, word);
     }
-    w.g.stb(0, 0, n, q - rest);
+    w.g.template stb<POL>(0, 0, n, q - rest);
   } else {
 #pragma unroll
-    for (int i = 0; i < 19; ++i) w.g.stb(i, 0, n, gg[i]);
+    for (int i = 0; i < 19; ++i) w.g.template stb<POL>(i, 0, n, gg[i]);
   }
+}
+
+template <int POL, int P, bool BIG, typename T>
+__device__ __forceinline__ void f_store(const PopView<P, BIG>& w, uint32_t n, const T f[19]) {
+#pragma unroll
+  for (int i = 0; i < 19; ++i) w.f.template stb<POL>(i, 0, n, f[i]);
 }
 
 // Order parameter over the tiles.
@@ -268,7 +274,7 @@ __device__ __forceinline__ void tile_state(const Planes<typename PrecT<P>::T, fa
 // Second launch of a step: force, velocity and pressure of the tile and f's
 // collision, which needs no grad p. Writes f, mu, p and j, which the third
 // launch needs. 117 registers in FP64: two 512-lane workgroups per CU.
-template <int P, bool BIG, bool TRT, int TX, int TY, int TZ>
+template <int P, bool BIG, bool TRT, int POL, int TX, int TY, int TZ>
 __global__ __launch_bounds__(TX * TY * TZ) void k3_tile_f(
     Pop3<P> in, Pop3<P> out, const typename PrecT<P>::T* __restrict__ phi,
     typename PrecT<P>::T* __restrict__ mu, typename PrecT<P>::T* __restrict__ p,
@@ -302,8 +308,7 @@ __global__ __launch_bounds__(TX * TY * TZ) void k3_tile_f(
   for (int i = 0; i < 19; ++i) gd[i] = T(0);
   if constexpr (TRT) collide3_trt<T>(f, gd, m, dp0, c.c);
   else collide3<T>(f, gd, m, dp0, c.c);
-#pragma unroll
-  for (int i = 0; i < 19; ++i) w.f.stb(i, 0, n, f[i]);
+  f_store<POL>(w, n, f);
 }
 
 // The requested moments (binary64 fields) of the tile.
@@ -338,7 +343,7 @@ __global__ __launch_bounds__(TX * TY * TZ) void k3_tile_macro(
 // Third launch of a step: collides g of the tile with grad p (p staged in LDS
 // over the tile and one node around it, like mu), u and F re-formed from j
 // and grad mu as the second launch formed them.
-template <int P, bool BIG, int TX, int TY, int TZ>
+template <int P, bool BIG, int POL, int TX, int TY, int TZ>
 __global__ __launch_bounds__(TX * TY * TZ) void k3_tile_g(
     Pop3<P> in, Pop3<P> out, const typename PrecT<P>::T* __restrict__ phi,
     const typename PrecT<P>::T* __restrict__ mu, const typename PrecT<P>::T* __restrict__ p,
@@ -387,7 +392,7 @@ __global__ __launch_bounds__(TX * TY * TZ) void k3_tile_g(
 #pragma unroll
   for (int i = 0; i < 19; ++i) fd[i] = T(0);
   collide3<T>(fd, gg, m, dp, c.c);
-  g_store<P, BIG, T>(w, n, gg, q);
+  g_store<POL>(w, n, gg, q);
 }
 
 // Position r of the shell of one node around the tile: the two layers below
@@ -507,9 +512,8 @@ __global__ __launch_bounds__(NT) void k3_tile_step(
   if constexpr (TRT) collide3_trt<T>(f, gg, m, dp, c.c);
   else collide3<T>(f, gg, m, dp, c.c);
   const uint32_t n = tself(k);
-#pragma unroll
-  for (int i = 0; i < 19; ++i) w.f.stb(i, 0, n, f[i]);
-  g_store<P, BIG, T>(w, n, gg, q);
+  f_store<ST_BACK>(w, n, f);
+  g_store<ST_BACK>(w, n, gg, q);
 }
 
 }  // namespace qilbm3

@@ -254,15 +254,19 @@ __device__ __forceinline__ S buf_ld(__amdgpu_buffer_rsrc_t r, uint32_t voff, uin
     return __builtin_bit_cast(S, __builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0));
   }
 }
-template <typename S>
+// Cache policy of a store (the buffer instruction's bits): written back when
+// the line leaves L2, written through to memory (sc1), or streaming (nt).
+enum StorePolicy : int { ST_BACK = 0, ST_STREAM = 2, ST_THROUGH = 16 };
+
+template <typename S, int POL = ST_BACK>
 __device__ __forceinline__ void buf_st(S v, __amdgpu_buffer_rsrc_t r, uint32_t voff,
                                        uint32_t soff) {
   if constexpr (sizeof(S) == 8) {
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, POL);
   } else if constexpr (sizeof(S) == 4) {
-    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, voff, soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, voff, soff, POL);
   } else {
-    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, voff, soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, voff, soff, POL);
   }
 }
 

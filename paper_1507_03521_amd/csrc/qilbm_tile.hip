@@ -116,21 +116,21 @@ __device__ __forceinline__ typename PrecT<P>::T g_words_phi(const typename GWord
 }
 
 // Stores a node's words at element n.
-template <int P, int I = 0>
+template <int P, int POL, int I = 0>
 __device__ __forceinline__ void tile_store(__amdgpu_buffer_rsrc_t rs, uint32_t Ns, uint32_t n,
                                            const Row<P>& row) {
   if constexpr (I < 9) {
     if constexpr (P == P_F64) {
-      buf_st<double>(row.f[I], rs, n * 8u, PlaneOf<P, false, I>::at(Ns));
-      buf_st<double>(row.g[I], rs, n * 8u, PlaneOf<P, true, I>::at(Ns));
+      buf_st<double, POL>(row.f[I], rs, n * 8u, PlaneOf<P, false, I>::at(Ns));
+      buf_st<double, POL>(row.g[I], rs, n * 8u, PlaneOf<P, true, I>::at(Ns));
     } else if constexpr (P == P_F16 && I == 0) {
-      buf_st<__half>(__builtin_bit_cast(__half, (uint16_t)row.f0), rs, n * 2u, 0);
-      buf_st<uint32_t>(row.w[0], rs, n * 4u, PlaneOf<P, true, 0>::at(Ns));
+      buf_st<__half, POL>(__builtin_bit_cast(__half, (uint16_t)row.f0), rs, n * 2u, 0);
+      buf_st<uint32_t, POL>(row.w[0], rs, n * 4u, PlaneOf<P, true, 0>::at(Ns));
     } else {
-      buf_st<typename BufT<P>::R>(row.w[I], rs, n * PlaneOf<P, true, I>::size,
+      buf_st<typename BufT<P>::R, POL>(row.w[I], rs, n * PlaneOf<P, true, I>::size,
                                   PlaneOf<P, true, I>::at(Ns));
     }
-    tile_store<P, I + 1>(rs, Ns, n, row);
+    tile_store<P, POL, I + 1>(rs, Ns, n, row);
   }
 }
 
@@ -200,7 +200,7 @@ template <int P, int N> struct MidOf<1, P, N> { struct T {}; };
 // (x < nx, y < ny) go to `out`. LDS element of interior node (lx, ly):
 // (ly + 3) PX + lx + 3.
 template <int P, int IX, int IY, int PX, int PY, int NT, int NM_, bool FROM_MID, bool TO_MID,
-          bool EDGE, bool TRT, typename MID>
+          bool EDGE, bool TRT, int POL, typename MID>
 __device__ __forceinline__ void tile_phase(__amdgpu_buffer_rsrc_t rin, __amdgpu_buffer_rsrc_t rout,
                                            const Coef<typename PrecT<P>::T>& c, const Geom& g,
                                            int bx, int by, int ox, int TXr, int TYr,
@@ -308,7 +308,7 @@ __device__ __forceinline__ void tile_phase(__amdgpu_buffer_rsrc_t rin, __amdgpu_
     Row<P> o;
     row_pack<P>(f, gg, phi_q, o);
     if constexpr (TO_MID) mid_put<P, NM_>(M, ly * IX + lx, o);
-    else if (owns) tile_store<P>(rout, Ns, (uint32_t)n, o);
+    else if (owns) tile_store<P, POL>(rout, Ns, (uint32_t)n, o);
   }
 }
 
@@ -319,7 +319,7 @@ __device__ __forceinline__ void tile_phase(__amdgpu_buffer_rsrc_t rin, __amdgpu_
 // they are written is a uniform branch and not a variant of the kernel: the
 // compiler contracts multiply-adds per kernel, and a recording replay must
 // reproduce the plain steps bit for bit.
-template <int P, int K, int TX, int TY, int NT, bool TRT>
+template <int P, int K, int TX, int TY, int NT, bool TRT, int POL>
 __global__ __launch_bounds__(NT) void k_tile(Pop<P> in, Pop<P> out, Coef<typename PrecT<P>::T> c,
                                              Geom g, int ntx, uint32_t bytes,
                                              typename PrecT<P>::T* rec0,
@@ -341,24 +341,24 @@ __global__ __launch_bounds__(NT) void k_tile(Pop<P> in, Pop<P> out, Coef<typenam
   const bool edge = g.walls && (y0 - O - 3 <= 0 || y0 + TY + O + 3 >= g.ny);
   if constexpr (K == 2) {
     if (edge) {
-      tile_phase<P, TX + 8, TY + 8, PX, PY, NT, NM_, false, true, true, TRT>(
+      tile_phase<P, TX + 8, TY + 8, PX, PY, NT, NM_, false, true, true, TRT, POL>(
           rin, rout, c, g, x0 - 4, y0 - 4, 4, TX, TY, rec0, L, M);
       __syncthreads();
-      tile_phase<P, TX, TY, PX, PY, NT, NM_, true, false, true, TRT>(
+      tile_phase<P, TX, TY, PX, PY, NT, NM_, true, false, true, TRT, POL>(
           rin, rout, c, g, x0, y0, 0, TX, TY, rec1, L, M);
     } else {
-      tile_phase<P, TX + 8, TY + 8, PX, PY, NT, NM_, false, true, false, TRT>(
+      tile_phase<P, TX + 8, TY + 8, PX, PY, NT, NM_, false, true, false, TRT, POL>(
           rin, rout, c, g, x0 - 4, y0 - 4, 4, TX, TY, rec0, L, M);
       __syncthreads();
-      tile_phase<P, TX, TY, PX, PY, NT, NM_, true, false, false, TRT>(
+      tile_phase<P, TX, TY, PX, PY, NT, NM_, true, false, false, TRT, POL>(
           rin, rout, c, g, x0, y0, 0, TX, TY, rec1, L, M);
     }
   } else {
     if (edge)
-      tile_phase<P, TX, TY, PX, PY, NT, NM_, false, false, true, TRT>(
+      tile_phase<P, TX, TY, PX, PY, NT, NM_, false, false, true, TRT, POL>(
           rin, rout, c, g, x0, y0, 0, TX, TY, rec0, L, M);
     else
-      tile_phase<P, TX, TY, PX, PY, NT, NM_, false, false, false, TRT>(
+      tile_phase<P, TX, TY, PX, PY, NT, NM_, false, false, false, TRT, POL>(
           rin, rout, c, g, x0, y0, 0, TX, TY, rec0, L, M);
   }
 }
@@ -369,7 +369,7 @@ __global__ __launch_bounds__(NT) void k_tile(Pop<P> in, Pop<P> out, Coef<typenam
 //   64 x 64      49.4 -> 3.75   33.2 -> 3.17   34.3 -> 4.44
 //   128 x 128    53.0 -> 4.27   35.2 -> 3.48   35.7 -> 4.52
 //   256 x 256    52.8 -> 6.01   35.4 -> 4.31   35.3 -> 4.99
-//   256 x 1024   53.1 -> 16.8   35.7 -> 9.55   36.1 -> 8.45
+//   256 x 1024   53.1 -> 15.5   35.7 -> 9.0    36.1 -> 8.1
 //   701 x 1333   59.1 -> 68.4   38.2 -> 25.3   39.1 -> 21.8
 //   1001 x 2003   121 -> 182    53.1 -> 83.0   58.4 -> 43.7
 //   2048 x 2048   210 -> 317    91.6 -> 179     103 -> 116
@@ -379,24 +379,42 @@ __global__ __launch_bounds__(NT) void k_tile(Pop<P> in, Pop<P> out, Coef<typenam
 // is the fastest: 8 x 4 up to 64 x 128, 16 x 4 up to 128 x 128, 32 x 8 up to
 // 256 x 256 (fp64, 64 x 64: 3.75, 3.96, 5.20 us; 128 x 128: 4.92, 4.27, 5.44;
 // 256 x 256: 10.0, 11.2, 6.01). Beyond, the doubled halo costs more than a
-// launch (256 x 1024, fp64: two steps 18.2, one 16.8) and a pair of steps is
+// launch (256 x 1024, fp64: two steps 18.2, one 15.5) and a pair of steps is
 // two launches.
-template <int P, int K, int TX, int TY, int NT, bool TRT>
+template <int P, int K, int TX, int TY, int NT, bool TRT, int POL>
 void launch_tile(const void* pin, void* pout, const Coef<typename PrecT<P>::T>& c, const Geom& g,
                  void* rec0, void* rec1, hipStream_t s) {
   using T = typename PrecT<P>::T;
   const Pop<P> i{(char*)pin, g.Ns}, o{(char*)pout, g.Ns};
-  hipLaunchKernelGGL((k_tile<P, K, TX, TY, NT, TRT>), dim3(tiles(g, TX, TY)), dim3(NT), 0, s,
+  hipLaunchKernelGGL((k_tile<P, K, TX, TY, NT, TRT, POL>), dim3(tiles(g, TX, TY)), dim3(NT), 0, s,
                      i, o, c, g, (g.nx + TX - 1) / TX, (uint32_t)pop_bytes(P, g.Ns), (T*)rec0,
                      (T*)rec1);
+}
+
+// Whether the one-step kernel writes its results through. Lines that a kernel leaves
+// dirty in the XCDs' L2 (4 MB each) are written back when it ends, with
+// nothing to overlap that: written through, they leave as they are made (fp64
+// 256 x 1024 17.1 us a step, 15.5 through; fp32 9.7, 9.0; 512 x 1024 28.6, 27.8;
+// 640 x 1000 34.4 and 33.9 to 35.0: the end is a small part by then). A row that does not start on a 128-byte line has its tiles share
+// lines, which then are written in parts, twice (fp64 1001 x 700 36.6, 40.0
+// through; fp32 701 x 1333 25.9, 27.4), and still gains while the lattice is
+// small (fp64 500 x 500 16.5, 15.0; 301 x 701 14.7, 14.3).
+bool tile_through(const Geom& g) {
+  return g.N <= (g.nx % 16 == 0 ? 600000 : 300000);
 }
 
 template <int P, int K, int TX, int TY, int NT>
 hipError_t launch_tile_variant(const void* pin, void* pout, const Coef<typename PrecT<P>::T>& c,
                                const Geom& g, void* rec0, void* rec1, hipStream_t s, bool trt) {
   if (trt && (rec0 || rec1)) return hipErrorInvalidValue;       // no recording TRT variant
-  if (trt) launch_tile<P, K, TX, TY, NT, true>(pin, pout, c, g, nullptr, nullptr, s);
-  else launch_tile<P, K, TX, TY, NT, false>(pin, pout, c, g, rec0, rec1, s);
+  constexpr int THROUGH = K == 1 ? ST_THROUGH : ST_BACK;
+  if (tile_through(g)) {
+    if (trt) launch_tile<P, K, TX, TY, NT, true, THROUGH>(pin, pout, c, g, nullptr, nullptr, s);
+    else launch_tile<P, K, TX, TY, NT, false, THROUGH>(pin, pout, c, g, rec0, rec1, s);
+  } else {
+    if (trt) launch_tile<P, K, TX, TY, NT, true, ST_BACK>(pin, pout, c, g, nullptr, nullptr, s);
+    else launch_tile<P, K, TX, TY, NT, false, ST_BACK>(pin, pout, c, g, rec0, rec1, s);
+  }
   return hipGetLastError();
 }
 
