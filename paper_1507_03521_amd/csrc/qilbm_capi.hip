@@ -98,8 +98,7 @@ Layout layout(const lbm_params* p) {
   const Geom g = make_geom(p);
   Layout L;
   const size_t pb = up((size_t)pop_bytes(p->precision, g.Ns));
-  L.nred = (int)((g.N + 255) / 256);
-  if (L.nred > 2048) L.nred = 2048;
+  L.nred = mass_blocks(g);
   L.pop0 = 0;
   L.pop1 = L.pop0 + pb;
   L.fields = L.pop1 + pb;
@@ -226,6 +225,8 @@ template <int P>
 lbm_status moments_p(lbm_ctx* c, const MomentOut& mo) {
   using T = typename PrecT<P>::T;
   const Coef<T> k = coef_t<T>(c);
+  if (moments_fit<P>(c->geom))
+    return st(launch_moments<P>(c->pop[c->cur], mo, k, c->geom, c->stream));
   hipError_t e = launch_fields<P>(c->pop[c->cur], phi_f(c), mu_f(c), k, c->geom, c->stream);
   if (e != hipSuccess) return LBM_EDEVICE;
   return st(launch_macro<P>(c->pop[c->cur], phi_f(c), mu_f(c), nullptr, nullptr, mo, k, c->geom,
@@ -245,7 +246,7 @@ lbm_status mass_p(lbm_ctx* c) {
 // device array instead of a context workspace.
 constexpr int64_t NOALLOC_MAX_NODES = int64_t(1) << 21;
 constexpr size_t NOALLOC_FIELD_BYTES = size_t(NOALLOC_MAX_NODES) * 8;
-constexpr int NOALLOC_MAX_PARTS = 2048;   // the workspace layout's cap of nred
+constexpr int NOALLOC_MAX_PARTS = MASS_BLOCKS;
 constexpr size_t NOALLOC_BYTES = 2 * NOALLOC_FIELD_BYTES + size_t(NOALLOC_MAX_PARTS) * 4 * 8;
 
 }  // namespace
@@ -284,12 +285,10 @@ hipError_t mass_noalloc_p(const lbm_params& p, const void* state, double* out, c
   double d[6];
   derive(&p, d);
   const Geom g = make_geom(&p);
-  // same partial count as a context's workspace (layout()), so the totals
-  // are those of lbm_mass bit for bit
-  int nred = (int)((g.N + 255) / 256);
-  if (nred > NOALLOC_MAX_PARTS) nred = NOALLOC_MAX_PARTS;
+  // the partial count of a context's workspace (layout()), so the totals are
+  // those of lbm_mass bit for bit
   return launch_mass<P>(state, sc, sc + NOALLOC_FIELD_BYTES, (double*)(sc + 2 * NOALLOC_FIELD_BYTES),
-                        nred, out, coef_of<T>(p, d), coef_of<double>(p, d), g, s);
+                        mass_blocks(g), out, coef_of<T>(p, d), coef_of<double>(p, d), g, s);
 }
 
 }  // namespace

@@ -106,6 +106,19 @@ template <int P>
 hipError_t launch_step2_tile(const void* pin, void* pout, const Coef<typename PrecT<P>::T>& c,
                              const Geom& g, void* rec0, void* rec1, hipStream_t s, bool trt);
 
+// FP64 moments into mo in one pass, where moments_fit (else launch_fields and
+// launch_macro).
+template <int P>
+bool moments_fit(const Geom& g);
+template <int P>
+hipError_t launch_moments(const void* pop, const MomentOut& mo,
+                          const Coef<typename PrecT<P>::T>& c, const Geom& g, hipStream_t s);
+// Partials of the totals: mass_blocks(g) rows of four in launch_mass.
+constexpr int MASS_BLOCKS = 2048;
+int mass_blocks(const Geom& g);
+template <int P>
+hipError_t launch_mass_tiles(const void* pop, double* part, const Coef<typename PrecT<P>::T>& c,
+                             const Coef<double>& c64, const Geom& g, hipStream_t s);
 template <int P>
 hipError_t launch_mass(const void* pop, void* phi, void* mu, double* part, int nred, double* out,
                        const Coef<typename PrecT<P>::T>& c, const Coef<double>& c64,

@@ -266,28 +266,6 @@ __global__ __launch_bounds__(256) void k_collide(Pop<P> in, Pop<P> out,
 // Per-block FP64 partials of (sum phi, sum rho, sum rho ux, sum rho uy) over
 // a fixed node-to-thread assignment, reduced with wave64 shuffles; a single
 // block then adds the partials in a fixed order. Bitwise reproducible.
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  return v;
-}
-
-__device__ __forceinline__ void block_sum4(double a[4], double* out) {
-  __shared__ double red[4][4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) a[k] = wave_sum(a[k]);
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) red[wave][k] = a[k];
-  }
-  __syncthreads();
-  if (threadIdx.x < 4) {
-    const int k = threadIdx.x;
-    out[k] = (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
-  }
-}
-
 template <int P>
 __global__ __launch_bounds__(256) void k_mass_partial(Pop<P> in,
                                                       const typename PrecT<P>::T* __restrict__ phi,
@@ -1416,11 +1394,17 @@ hipError_t launch_mass(const void* pop, void* phi, void* mu, double* part, int n
                        const Coef<typename PrecT<P>::T>& c, const Coef<double>& c64,
                        const Geom& g, hipStream_t s) {
   using T = typename PrecT<P>::T;
-  hipError_t e = launch_fields<P>(pop, phi, mu, c, g, s);
-  if (e != hipSuccess) return e;
-  Pop<P> i{(char*)pop, g.Ns};
-  hipLaunchKernelGGL(k_mass_partial<P>, dim3(nred), dim3(256), 0, s, i, (const T*)phi,
-                     (const T*)mu, part, c, c64.rho_B, c64.drho, g);
+  hipError_t e;
+  if (moments_fit<P>(g)) {
+    e = launch_mass_tiles<P>(pop, part, c, c64, g, s);
+    if (e != hipSuccess) return e;
+  } else {
+    e = launch_fields<P>(pop, phi, mu, c, g, s);
+    if (e != hipSuccess) return e;
+    Pop<P> i{(char*)pop, g.Ns};
+    hipLaunchKernelGGL(k_mass_partial<P>, dim3(nred), dim3(256), 0, s, i, (const T*)phi,
+                       (const T*)mu, part, c, c64.rho_B, c64.drho, g);
+  }
   hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, s, (const double*)part, nred, 4, out);
   return hipGetLastError();
 }

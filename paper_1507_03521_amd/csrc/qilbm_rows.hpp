@@ -321,4 +321,28 @@ __device__ __forceinline__ void row_pack(const typename PrecT<P>::T f[9],
   }
 }
 
+// Sum of a wave's values (lane 0), and of four values over a workgroup of 256
+// lanes into out[0..3], in a fixed order.
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+  return v;
+}
+
+__device__ __forceinline__ void block_sum4(double a[4], double* out) {
+  __shared__ double red[4][4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) a[k] = wave_sum(a[k]);
+  if (lane == 0) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) red[wave][k] = a[k];
+  }
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    const int k = threadIdx.x;
+    out[k] = (red[0][k] + red[1][k]) + (red[2][k] + red[3][k]);
+  }
+}
+
 }  // namespace qilbm

@@ -363,6 +363,155 @@ __global__ __launch_bounds__(NT) void k_tile(Pop<P> in, Pop<P> out, Coef<typenam
   }
 }
 
+// -------------------------------------------------- moments and totals
+// State m of the thread's node of a TX x TY tile (one node per lane): phi
+// over the tile and two nodes around it from the pulled g, mu over the tile
+// and one node around it, force, velocity and pressure from the pulled f.
+template <int P, int TX, int TY, bool EDGE>
+__device__ __forceinline__ void tile_macro(__amdgpu_buffer_rsrc_t rin,
+                                           const Coef<typename PrecT<P>::T>& c, const Geom& g,
+                                           int x0, int y0, const TileNode& k, int lx, int ly,
+                                           typename PrecT<P>::T* lphi,
+                                           typename PrecT<P>::T* lmu, Row<P>& row,
+                                           Macro<typename PrecT<P>::T>& m) {
+  using T = typename PrecT<P>::T;
+  constexpr int NT = TX * TY, PX = TX + 4;
+  const int t = threadIdx.x, e = (ly + 2) * PX + lx + 2;
+  const uint32_t Ns = (uint32_t)g.Ns;
+  tile_load_dirs<P, EDGE>(rin, Ns, k, row);
+  for (int h = t; h < frame_count<TX, TY, 2>(); h += NT) {
+    int hx, hy;
+    frame_pos<TX, TY, 2>(h, hx, hy);
+    typename GWord<P>::T w[9];
+    tile_load_g<P, EDGE>(rin, Ns, tile_node(x0 + hx, y0 + hy, g), w);
+    lphi[(hy + 2) * PX + hx + 2] = g_words_phi<P>(w);
+  }
+  int32_t phi_q = 0;
+  const T ph = row_phi<P>(row, phi_q);
+  lphi[e] = ph;
+  __syncthreads();
+  T v[3][3], gphx, gphy, lapphi, gmux, gmuy, lapmu;
+  tile3x3<T, PX>(lphi, e, k.lo, k.hi, v);
+  stencil(v, gphx, gphy, lapphi);
+  const T mu = mu_bulk(ph, c) - c.kappa * lapphi;
+  lmu[e] = mu;
+  for (int h = t; h < frame_count<TX, TY, 1>(); h += NT) {
+    int hx, hy;
+    frame_pos<TX, TY, 1>(h, hx, hy);
+    const int y = y0 + hy, eh = (hy + 2) * PX + hx + 2;
+    T gx, gy, lap;
+    tile3x3<T, PX>(lphi, eh, g.walls && y <= 0, g.walls && y >= g.ny - 1, v);
+    stencil(v, gx, gy, lap);
+    lmu[eh] = mu_bulk(v[1][1], c) - c.kappa * lap;
+  }
+  __syncthreads();
+  T f[9], gg[9], S, jx, jy;
+  row_unpack<P>(row, f, gg);
+  moments9(f, S, jx, jy);
+  tile3x3<T, PX>(lmu, e, k.lo, k.hi, v);
+  stencil(v, gmux, gmuy, lapmu);
+  macro_node(ph, mu, gphx, gphy, gmux, gmuy, lapmu, S, jx, jy, c, m);
+}
+
+// The requested moments in one pass over the populations (the three launches
+// that form phi and mu as fields first read g, or its words' pairs, twice):
+// with four fields 2048 x 8192 fp32 589 -> 333 us, 5.2 TB/s, fp64 732 -> 569, fp16
+// 400 -> 276; on small lattices one launch instead of three.
+template <int P, int TX, int TY>
+__global__ __launch_bounds__(TX * TY) void k_tile_moments(Pop<P> in, MomentOut mo,
+                                                          Coef<typename PrecT<P>::T> c, Geom g,
+                                                          int ntx, uint32_t bytes) {
+  using T = typename PrecT<P>::T;
+  __shared__ T lphi[(TX + 4) * (TY + 4)];
+  __shared__ T lmu[(TX + 4) * (TY + 4)];
+  const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(in.base, 0, (int)bytes, BUF_WORD3);
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int ty = tile / ntx, tx = tile - ty * ntx;
+  const int x0 = tx * TX, y0 = ty * TY;
+  const int ly = threadIdx.x / TX, lx = threadIdx.x - ly * TX;
+  const TileNode k = tile_node(x0 + lx, y0 + ly, g);
+  Row<P> row;
+  Macro<T> m;
+  if (g.walls && (y0 - 2 <= 0 || y0 + TY + 2 >= g.ny))
+    tile_macro<P, TX, TY, true>(rin, c, g, x0, y0, k, lx, ly, lphi, lmu, row, m);
+  else
+    tile_macro<P, TX, TY, false>(rin, c, g, x0, y0, k, lx, ly, lphi, lmu, row, m);
+  if (x0 + lx >= g.nx || y0 + ly >= g.ny) return;
+  const int64_t n = (int64_t)k.r[1] + k.c[1];
+  if (mo.phi) mo.phi[n] = double(m.phi);
+  if (mo.rho) mo.rho[n] = double(m.rho);
+  if (mo.ux) mo.ux[n] = double(m.ux);
+  if (mo.uy) mo.uy[n] = double(m.uy);
+  if (mo.p) mo.p[n] = double(m.p);
+  if (mo.mu) mo.mu[n] = double(m.mu);
+}
+
+// phi alone needs no neighbours.
+template <int P>
+__global__ __launch_bounds__(256) void k_phi_out(Pop<P> in, double* __restrict__ phi, Geom g,
+                                                 uint32_t bytes) {
+  const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(in.base, 0, (int)bytes, BUF_WORD3);
+  const int64_t n = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
+  if (n >= g.N) return;
+  const int y = (int)((uint32_t)n / (uint32_t)g.nx), x = (int)((uint32_t)n - (uint32_t)y * g.nx);
+  typename GWord<P>::T w[9];
+  tile_load_g<P, true>(rin, (uint32_t)g.Ns, tile_node(x, y, g), w);
+  phi[n] = double(g_words_phi<P>(w));
+}
+
+// phi of a node's words exactly, in binary64 (summed like pull_phi_exact).
+template <int P, int I = 0>
+__device__ __forceinline__ double row_phi_exact(const Row<P>& row) {
+  if constexpr (I < 9) {
+    double v;
+    if constexpr (P == P_F64) v = row.g[I];
+    else v = double(BufPop<P>::template q_g<I>(row.w[I])) * GQI_D;
+    return v + row_phi_exact<P, I + 1>(row);
+  } else {
+    return 0.0;
+  }
+}
+
+// Per-workgroup partials of (sum phi, sum rho, sum rho ux, sum rho uy), each
+// over a contiguous share of the 32 x 8 tiles.
+constexpr int MASS_TX = 32, MASS_TY = 8;
+template <int P>
+__global__ __launch_bounds__(256) void k_tile_mass(Pop<P> in, double* __restrict__ part,
+                                                   Coef<typename PrecT<P>::T> c, double rho_B,
+                                                   double drho, Geom g, int ntx, int ntiles,
+                                                   uint32_t bytes) {
+  using T = typename PrecT<P>::T;
+  constexpr int TX = MASS_TX, TY = MASS_TY;
+  __shared__ T lphi[(TX + 4) * (TY + 4)];
+  __shared__ T lmu[(TX + 4) * (TY + 4)];
+  const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(in.base, 0, (int)bytes, BUF_WORD3);
+  const int b = xcd_tile(blockIdx.x, gridDim.x);
+  const int t0 = (int)((int64_t)ntiles * b / gridDim.x);
+  const int t1 = (int)((int64_t)ntiles * (b + 1) / gridDim.x);
+  const int ly = threadIdx.x / TX, lx = threadIdx.x - ly * TX;
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int tile = t0; tile < t1; ++tile) {
+    const int ty = tile / ntx, tx = tile - ty * ntx;
+    const int x0 = tx * TX, y0 = ty * TY;
+    const TileNode k = tile_node(x0 + lx, y0 + ly, g);
+    Row<P> row;
+    Macro<T> m;
+    if (g.walls && (y0 - 2 <= 0 || y0 + TY + 2 >= g.ny))
+      tile_macro<P, TX, TY, true>(rin, c, g, x0, y0, k, lx, ly, lphi, lmu, row, m);
+    else
+      tile_macro<P, TX, TY, false>(rin, c, g, x0, y0, k, lx, ly, lphi, lmu, row, m);
+    if (x0 + lx < g.nx && y0 + ly < g.ny) {
+      const double ph = row_phi_exact<P>(row);
+      a[0] += ph;
+      a[1] += rho_B + drho * ph;
+      a[2] += double(m.rho) * double(m.ux);
+      a[3] += double(m.rho) * double(m.uy);
+    }
+    __syncthreads();       // the next tile takes the LDS planes
+  }
+  block_sum4(a, part + 4 * blockIdx.x);
+}
+
 // ------------------------------------------------------------- dispatch
 // Measured on MI355X (us per step, row-sweeping kernel -> tiles; fp64 / fp32
 // at two steps per pass, fp16 storage at one):
@@ -466,8 +615,60 @@ hipError_t launch_step2_tile(const void* pin, void* pout, const Coef<typename Pr
   return launch_tile_variant<P, 2, 32, 8, 832>(pin, pout, c, g, rec0, rec1, s, trt);
 }
 
+// All byte offsets of a population buffer in 32 bits.
+template <int P>
+bool moments_fit(const Geom& g) {
+  return pop_bytes(P, g.Ns) <= (int64_t)UINT32_MAX;
+}
+
+template <int P, int TX, int TY>
+void launch_moments_tile(const Pop<P>& in, const MomentOut& mo,
+                         const Coef<typename PrecT<P>::T>& c, const Geom& g, hipStream_t s) {
+  hipLaunchKernelGGL((k_tile_moments<P, TX, TY>), dim3(tiles(g, TX, TY)), dim3(TX * TY), 0, s, in,
+                     mo, c, g, (g.nx + TX - 1) / TX, (uint32_t)pop_bytes(P, g.Ns));
+}
+
+template <int P>
+hipError_t launch_moments(const void* pop, const MomentOut& mo,
+                          const Coef<typename PrecT<P>::T>& c, const Geom& g, hipStream_t s) {
+  const Pop<P> in{(char*)pop, g.Ns};
+  if (mo.phi && !mo.rho && !mo.ux && !mo.uy && !mo.p && !mo.mu) {
+    hipLaunchKernelGGL(k_phi_out<P>, dim3((unsigned)((g.N + 255) / 256)), dim3(256), 0, s, in,
+                       mo.phi, g, (uint32_t)pop_bytes(P, g.Ns));
+    return hipGetLastError();
+  }
+  // 64 wide tiles of little halo where they are two rounds of workgroups and
+  // more (2048 x 8192, 64 x 16, 64 x 8, 32 x 8, 16 x 8: fp32 333, 358, 426, 515
+  // us; fp64 596, 569, 631, 711), else small ones
+  if (tiles(g, 64, 8) < 2 * CUS) launch_moments_tile<P, 16, 8>(in, mo, c, g, s);
+  else if (P == P_F32) launch_moments_tile<P, 64, 16>(in, mo, c, g, s);
+  else launch_moments_tile<P, 64, 8>(in, mo, c, g, s);
+  return hipGetLastError();
+}
+
+// Workgroups of the totals kernel, one partial each.
+int mass_blocks(const Geom& g) {
+  const int n = tiles(g, MASS_TX, MASS_TY);
+  return n < MASS_BLOCKS ? n : MASS_BLOCKS;
+}
+
+template <int P>
+hipError_t launch_mass_tiles(const void* pop, double* part, const Coef<typename PrecT<P>::T>& c,
+                             const Coef<double>& c64, const Geom& g, hipStream_t s) {
+  const Pop<P> in{(char*)pop, g.Ns};
+  hipLaunchKernelGGL(k_tile_mass<P>, dim3(mass_blocks(g)), dim3(256), 0, s, in, part, c, c64.rho_B,
+                     c64.drho, g, (g.nx + MASS_TX - 1) / MASS_TX, tiles(g, MASS_TX, MASS_TY),
+                     (uint32_t)pop_bytes(P, g.Ns));
+  return hipGetLastError();
+}
+
 #define QILBM_INSTANTIATE(P)                                                                     \
   template bool tile_fits<P>(const Geom&);                                                       \
+  template bool moments_fit<P>(const Geom&);                                                     \
+  template hipError_t launch_moments<P>(const void*, const MomentOut&,                           \
+                                        const Coef<PrecT<P>::T>&, const Geom&, hipStream_t);     \
+  template hipError_t launch_mass_tiles<P>(const void*, double*, const Coef<PrecT<P>::T>&,       \
+                                           const Coef<double>&, const Geom&, hipStream_t);       \
   template hipError_t launch_step_tile<P>(const void*, void*, const Coef<PrecT<P>::T>&,          \
                                           const Geom&, void*, hipStream_t, bool);
 

@@ -56,3 +56,42 @@ def test_tiles_match_oracle(nx, ny, bc, precision):
     assert ef < TOL[precision][0] and eg < TOL[precision][1]
     if fixed:
         assert q229_total(lat.save_raw(), precision, nx, ny) == before
+
+
+@pytest.mark.parametrize("nx,ny,bc,precision", [
+    (3, 3, wl.WALLS_Y, "fp64"), (17, 9, wl.PERIODIC, "fp32"), (31, 7, wl.WALLS_Y, "fp16"),
+    (511, 511, wl.WALLS_Y, "fp64"), (513, 500, wl.WALLS_Y, "fp64"), (577, 479, wl.PERIODIC, "fp32"),
+    (640, 497, wl.WALLS_Y, "fp32"), (515, 523, wl.WALLS_Y, "fp16")])
+def test_moments_and_totals_match_oracle(nx, ny, bc, precision):
+    """16 x 8 tiles of the moments on small lattices, 64 x 8 and (FP32) 64 x 16
+    from 512 tiles on, and totals of 32 x 8 tiles shared out over workgroups:
+    the moments of the state that the GPU holds. phi is one rounding of an
+    exact sum, rho two more. mu, u and p are sums of at most 30 terms, the
+    largest 20 times the result (a Laplacian of mu, itself one of phi): 30 x 20
+    roundings of the compute type, 7e-14 and 4e-5."""
+    from paper_1507_03521_amd import Lattice
+    print(f"case moments {nx}x{ny} bc={bc} {precision}", flush=True)
+    pb = wl.droplet64().with_(nx=nx, ny=ny, bc=bc, gx=2e-5, gy=-1e-5, rho_ref=0.3)
+    f, g = wl.random_state(nx, ny, seed=nx + 3 * ny)
+    lat = Lattice(pb.as_dict(), np.full((ny, nx), 0.5), precision=precision, device="cuda:0")
+    lat.set_state(f, g)
+    fs, gs = (t.cpu() for t in lat.get_state())
+    co = O.coefficients_of(pb)
+    ref = dict(zip(("phi", "rho", "ux", "uy", "p", "mu"), O.moments(fs, gs, co)))
+    got = lat.moments()
+    fp64 = precision == "fp64"
+    eps = 2.0 ** -24
+    tol = dict(phi=1e-14 if fp64 else 2 * eps, rho=1e-14 if fp64 else 4 * eps,
+               **dict.fromkeys(("mu", "p", "ux", "uy"), 7e-14 if fp64 else 4e-5))
+    for k, r in ref.items():
+        assert _rel(got[k], r) < tol[k], k
+    assert torch.equal(lat.moments(("phi",))["phi"], got["phi"])
+    t = lat.mass()
+    if precision == "fp16":
+        return                   # the totals take binary16 g as Q2.29 contributions
+    rho, n = ref["rho"], nx * ny
+    exact = (float(ref["phi"].sum()), float(rho.sum()), float((rho * ref["ux"]).sum()),
+             float((rho * ref["uy"]).sum()))
+    scale = (n, n, float((rho * ref["ux"]).abs().sum()), float((rho * ref["uy"]).abs().sum()))
+    for a, b, s, w in zip(t, exact, scale, (1e-14, 1e-14, tol["ux"], tol["uy"])):
+        assert abs(a - b) <= w * s
