@@ -1461,9 +1461,12 @@ int store_policy(const Geom3& g) {
 // 16, 33 to 48). Whole rows of 32 load fewer lines twice: 256^3 in FP64 3.06
 // ms a step against 3.15 in 16 x 4 x 4, FP32 (LBM_FLAG_UNFUSED) 1.54 against
 // 1.86; 48^3 33 us against 26.
+inline bool narrow_tiles(const Geom3& g) {
+  return (g.nx + 15) / 16 * 16 * 4 <= (g.nx + 31) / 32 * 32 * 3;
+}
 template <int P, typename Fn>
 hipError_t with_tile(const Geom3& g, Fn&& fn) {
-  const bool narrow = (g.nx + 15) / 16 * 16 * 4 <= (g.nx + 31) / 32 * 32 * 3;
+  const bool narrow = narrow_tiles(g);
   if (big3<P>(g)) {
     if (narrow) fn(Tile3<true, 16, 4, 4>{});
     else fn(Tile3<true, 32, 4, 4>{});
@@ -1472,6 +1475,10 @@ hipError_t with_tile(const Geom3& g, Fn&& fn) {
     else fn(Tile3<false, 32, 4, 4>{});
   }
   return hipGetLastError();
+}
+
+inline int64_t tile_lanes(const Geom3& g) {
+  return narrow_tiles(g) ? tile_count<16, 4, 4>(g) * 256 : tile_count<32, 4, 4>(g) * 512;
 }
 
 // Planes of the context's fields.
@@ -1659,17 +1666,17 @@ lbm_status step_p(lbm3_ctx* c, int64_t n) {
   const bool one = small_one<P>(g), two = small_two<P>(g);
   const bool unfused = c->prm.flags & LBM_FLAG_UNFUSED;
   if constexpr (P == P_F32) {
-    // The z-sweep takes some 13 us a plane of its segments and six more of
-    // warm-up (whatever the lattice, which only sets the segments' length),
-    // the three launches 93 us per million nodes. Measured, z-sweep and
-    // tiles: 128^3 183 and 194 us, 256 x 256 x 64 353 and 398, 256^3 1290
-    // and 1540; 128 x 128 x 64 103 and 96, 96^3 103 and 77, 65 x 130 x 130
-    // 178 and 127, 20 x 250 x 250 264 and 133.
+    // The z-sweep takes 10 us and more a plane of its segments and six more of
+    // warm-up (the lattice only sets the segments' length), the three launches
+    // 93 us per million lanes of their tiles. Measured, z-sweep and tiles:
+    // 128^3 183 and 194 us, 256 x 256 x 64 353 and 398, 256^3 1290 and 1540, 229 x
+    // 61 x 79 122 and 126; 128 x 128 x 64 103 and 96, 250 x 16 x 250 105 and 97,
+    // 96^3 103 and 77, 65 x 130 x 130 178 and 127, 20 x 250 x 250 264 and 133.
     if (!unfused && !one && !two) {
       if (c->resident == 0) c->resident = fused_resident3();
       if (c->resident <= 0) return LBM_EDEVICE;
       const Fz3Shape sh = fused_shape3(g, c->resident);
-      if (g.N > (int64_t)140000 * (sh.seg + 6)) return step_fused_p<P>(c, n, sh);
+      if (tile_lanes(g) > (int64_t)113000 * (sh.seg + 6)) return step_fused_p<P>(c, n, sh);
     }
   }
   c->phiq_ok = false;
