@@ -409,11 +409,10 @@ __device__ __forceinline__ int32_t store_pairs(const FusedCtx<P, BIG>& k, uint32
 
 template <int P, bool BIG, int I = 1>
 __device__ __forceinline__ int32_t store_g_rest(const FusedCtx<P, BIG>& k, uint32_t row,
-                                              const typename PrecT<P>::T gg[9],
-                                              uint32_t vb = 0) {
+                                              const typename PrecT<P>::T gg[9]) {
   if constexpr (I < 9) {
-    const int32_t q = k.out.template st_g<I>(gg[I], row, k.col[1], vb);
-    return q + store_g_rest<P, BIG, I + 1>(k, row, gg, vb);
+    const int32_t q = k.out.template st_g<I>(gg[I], row, k.col[1]);
+    return q + store_g_rest<P, BIG, I + 1>(k, row, gg);
   } else {
     return 0;
   }
@@ -421,11 +420,18 @@ __device__ __forceinline__ int32_t store_g_rest(const FusedCtx<P, BIG>& k, uint3
 
 template <int P, bool BIG, int I = 0>
 __device__ __forceinline__ void store_f(const FusedCtx<P, BIG>& k, uint32_t row,
-                                        const typename PrecT<P>::T f[9], uint32_t vb = 0) {
+                                        const typename PrecT<P>::T f[9]) {
   if constexpr (I < 9) {
-    k.out.template st_f<I>(f[I], row, k.col[1], vb);
-    store_f<P, BIG, I + 1>(k, row, f, vb);
+    k.out.template st_f<I>(f[I], row, k.col[1]);
+    store_f<P, BIG, I + 1>(k, row, f);
   }
+}
+
+template <bool BIG>
+__device__ __forceinline__ void store_g(const FusedCtx<P_F64, BIG>& k, uint32_t row,
+                                        const double gg[9]) {
+  store_g_rest<P_F64, BIG>(k, row, gg);
+  k.out.st_g0(gg[0], 0, row, k.col[1]);
 }
 
 // Stores a node's post-collision populations; in the fixed-point modes g_0
@@ -433,8 +439,7 @@ __device__ __forceinline__ void store_f(const FusedCtx<P, BIG>& k, uint32_t row,
 template <int P, bool BIG>
 __device__ __forceinline__ void store_row(const FusedCtx<P, BIG>& k, uint32_t row,
                                           const typename PrecT<P>::T f[9],
-                                          const typename PrecT<P>::T gg[9], int32_t phi_q,
-                                          uint32_t vb = 0) {
+                                          const typename PrecT<P>::T gg[9], int32_t phi_q) {
   if constexpr (P == P_F16) {
     k.out.template st_f<0>(f[0], row, k.col[1]);
     const int32_t rest = store_pairs<P, BIG>(k, row, f, gg);
@@ -443,9 +448,9 @@ __device__ __forceinline__ void store_row(const FusedCtx<P, BIG>& k, uint32_t ro
     const int32_t rest = store_pairs<P, BIG>(k, row, f, gg);
     k.out.template st_pair_q<0>(f[0], phi_q - rest, row, k.col[1]);
   } else {
-    store_f<P, BIG>(k, row, f, vb);
-    const int32_t rest = store_g_rest<P, BIG>(k, row, gg, vb);
-    k.out.st_g0(gg[0], phi_q - rest, row, k.col[1], vb);
+    store_f<P, BIG>(k, row, f);
+    const int32_t rest = store_g_rest<P, BIG>(k, row, gg);
+    k.out.st_g0(gg[0], phi_q - rest, row, k.col[1]);
   }
 }
 
@@ -805,41 +810,24 @@ __device__ __forceinline__ void store_words(const FusedCtx<P, BIG>& k, uint32_t 
 // Row y's words from memory (pull streaming as in pull_row).
 template <int P, bool BIG>
 __device__ __forceinline__ void load_row(const FusedCtx<P, BIG>& k, int y, Row<P>& row) {
-  if constexpr (P == P_F64) {
-    pull_row<P, BIG, false>(k, y, row.f);
-    pull_row<P, BIG, true>(k, y, row.g);
-  } else {
-    pull_row<P, BIG, true>(k, y, row.w);
-    if constexpr (P == P_F16) row.f0 = pull_f0(k, y);
-  }
+  pull_row<P, BIG, true>(k, y, row.w);
+  if constexpr (P == P_F16) row.f0 = pull_f0(k, y);
 }
 
 // Stores a node's post-collision populations to memory.
 template <int P, bool BIG>
 __device__ __forceinline__ void store_node2(const FusedCtx<P, BIG>& k, uint32_t rowoff,
                                             const typename PrecT<P>::T f[9],
-                                            const typename PrecT<P>::T g[9], int32_t phi_q,
-                                            uint32_t vb = 0) {
-  if constexpr (P == P_F64) {
-    store_row<P, BIG>(k, rowoff, f, g, 0, vb);
-  } else {
-    Row<P> o;
-    pack_row<P>(f, g, phi_q, o.w, o.f0);
-    store_words<P, BIG>(k, rowoff, o.w, o.f0);
-  }
+                                            const typename PrecT<P>::T g[9], int32_t phi_q) {
+  Row<P> o;
+  pack_row<P>(f, g, phi_q, o.w, o.f0);
+  store_words<P, BIG>(k, rowoff, o.w, o.f0);
 }
 
 template <int P, int NT>
 __device__ __forceinline__ void ring_put(MidRing<P, NT>& M, int s, int lc, const Row<P>& row) {
 #pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    if constexpr (P == P_F64) {
-      M.f[s][i][lc] = row.f[i];
-      M.g[s][i][lc] = row.g[i];
-    } else {
-      M.w[s][i][lc] = row.w[i];
-    }
-  }
+  for (int i = 0; i < 9; ++i) M.w[s][i][lc] = row.w[i];
   if constexpr (P == P_F16) M.f0[s][lc] = (uint16_t)row.f0;
 }
 
@@ -855,12 +843,7 @@ __device__ __forceinline__ void pull_mid_dirs(const MidRing<P, NT>& M, const int
   if constexpr (I < 9) {
     constexpr int cx = CXS(I), cy = CYS(I);
     const int s = sl[1 - cy];
-    if constexpr (P == P_F64) {
-      row.f[I] = (&M.f[s][I][lc - 1])[1 - cx];
-      row.g[I] = (&M.g[s][I][lc - 1])[1 - cx];
-    } else {
-      row.w[I] = (&M.w[s][I][lc - 1])[1 - cx];
-    }
+    row.w[I] = (&M.w[s][I][lc - 1])[1 - cx];
     pull_mid_dirs<P, NT, I + 1>(M, sl, lc, row);
   }
 }
@@ -871,12 +854,7 @@ __device__ __forceinline__ void bounce_mid_dirs(const MidRing<P, NT>& M, int s1,
   if constexpr (I < 9) {
     constexpr int cy = CYS(I);
     if constexpr ((WALL == -1 && cy == 1) || (WALL == 1 && cy == -1)) {
-      if constexpr (P == P_F64) {
-        row.f[I] = M.f[s1][OPP(I)][lc];
-        row.g[I] = M.g[s1][OPP(I)][lc];
-      } else {
-        row.w[I] = M.w[s1][OPP(I)][lc];
-      }
+      row.w[I] = M.w[s1][OPP(I)][lc];
     }
     bounce_mid_dirs<P, NT, WALL, I + 1>(M, s1, lc, row);
   }
@@ -1056,44 +1034,20 @@ __device__ __forceinline__ void fused2_iter(const FusedCtx<P, BIG>& k, int r, in
     int32_t phi_q;
     row_phi<P>(rb1[(J + 1) & 3], phi_q);
     row_unpack<P>(rb1[(J + 1) & 3], f, gg);
-    // FP32 and FP16 storage issue the loads of row r + d before this
-    // collision, to hide their latency behind it; FP64 after it, once the
-    // row's words are dead: loading into registers still in use made the
-    // compiler copy the whole 18-word row each iteration (0.85 -> 0.79 ms
-    // per step), more than the latency costs there.
-    if constexpr (P != P_F64)
-      if (in_stage(k, r + d, 0)) load_row<P, BIG>(k, phys_row(r + d, g), rb1[(J + 1) & 3]);
+    // the loads of row r + d go out before this collision, which hides their
+    // latency
+    if (in_stage(k, r + d, 0)) load_row<P, BIG>(k, phys_row(r + d, g), rb1[(J + 1) & 3]);
     if (in_stage(k, cr, 3)) {
       stage_collide<T, NT, TRT>(L.s1, cr, g, lc, k.c, nd1[(J + 1) & 1], f, gg);
       Row<P2> o;
       row_pack<P2>(f, gg, phi_q, o);
       ring_put<P2, NT>(L.mid, s, lc, o);
     }
-    if constexpr (P == P_F64)
-      if (in_stage(k, r + d, 0)) load_row<P, BIG>(k, phys_row(r + d, g), rb1[(J + 1) & 3]);
   }
   // D2: row r - 8d to memory
   {
     const int cr = r2 - 3 * d;
-    if constexpr (P == P_F64 && !BIG) {
-      // Every lane issues the 18 stores; lanes and rows outside the stage
-      // offset theirs 2 GiB beyond the descriptors (each spans at most
-      // 2 GiB here, fused_big), where the hardware drops them. With the
-      // stores under a branch the compiler's count of memory operations in
-      // flight is merged from the path without them, and the next
-      // iteration's wait for the loads of row r + d would also wait for
-      // these stores (one wave per SIMD: nothing else covers it).
-      const bool ok = in_stage(k, cr, 7);
-      T f[9], gg[9];
-      int32_t phi_q = 0;
-      if (ok) {
-        row_phi<P2>(rb2[(J + 1) & 3], phi_q);
-        row_unpack<P2>(rb2[(J + 1) & 3], f, gg);
-        stage_collide<T, NT, TRT>(L.s2, cr, g, lc, k.c, nd2[(J + 1) & 1], f, gg);
-      }
-      const int crs = cr >= 0 && cr < g.ny ? cr : 0;
-      store_node2<P, BIG>(k, (uint32_t)(crs * g.nx), f, gg, phi_q, ok ? 0u : 0x80000000u);
-    } else if (in_stage(k, cr, 7)) {
+    if (in_stage(k, cr, 7)) {
       T f[9], gg[9];
       int32_t phi_q;
       row_phi<P2>(rb2[(J + 1) & 3], phi_q);
@@ -1105,22 +1059,12 @@ __device__ __forceinline__ void fused2_iter(const FusedCtx<P, BIG>& k, int r, in
   __syncthreads();
 }
 
-// Resident workgroups per CU (waves per SIMD with 4-wave workgroups): two
-// for FP32 and FP16 storage (LDS 78 KB / 53 KB, 245 / 216 VGPRs), one for
-// FP64 (LDS 156 KB: the ring of 18 binary64 words per node is 108 KB).
-template <int P> struct Fused2Waves { static constexpr int value = 2; };
-template <> struct Fused2Waves<P_F64> { static constexpr int value = 1; };
-
-// REC: also writes the records of the two states the pass starts from
-// (rec0: the state read, rec1: the state after the first step).
-template <int P, bool BIG, bool REC, bool TRT = false>
-__global__ __launch_bounds__(256, Fused2Waves<P>::value) void k_step2_fused(
-    Pop<P> in, Pop<P> out, Coef<typename PrecT<P>::T> c, Geom g, int width, int nstrips,
-    int seg_len, typename PrecT<P>::T* rec0, typename PrecT<P>::T* rec1) {
-  using T = typename PrecT<P>::T;
-  constexpr int NT = 256;
-  __shared__ Fused2Lds<P, NT> L;
-  FusedCtx<P, BIG> k;
+// The strip and segment of a two-step workgroup, and its lane t.
+template <int P, bool BIG>
+__device__ __forceinline__ void fused2_ctx(FusedCtx<P, BIG>& k, const Pop<P>& in,
+                                           const Pop<P>& out,
+                                           const Coef<typename PrecT<P>::T>& c, const Geom& g,
+                                           int width, int nstrips, int seg_len, int t) {
   k.in.init(in);
   k.out.init(out);
   k.c = c;
@@ -1133,7 +1077,6 @@ __global__ __launch_bounds__(256, Fused2Waves<P>::value) void k_step2_fused(
   k.y0 = seg * seg_len;
   k.y1 = min(g.ny, k.y0 + seg_len);
   k.d = (seg & 1) ? -1 : 1;
-  const int t = threadIdx.x;
   k.act = t < k.wi + 2 * FH2;
   k.lc = k.act ? t : FH2;
   // the halo reaches 7 columns beyond the strip: wrap with a full modulo
@@ -1143,6 +1086,21 @@ __global__ __launch_bounds__(256, Fused2Waves<P>::value) void k_step2_fused(
   k.col[0] = (uint32_t)wrap_x(k.x - 1, g.nx);
   k.col[1] = (uint32_t)k.x;
   k.col[2] = (uint32_t)wrap_x(k.x + 1, g.nx);
+}
+
+// FP32 and FP16 storage, two workgroups of four waves per CU (LDS 78 KB / 53 KB,
+// 245 / 216 VGPRs); FP64 runs k_step2_split.
+// REC: also writes the records of the two states the pass starts from
+// (rec0: the state read, rec1: the state after the first step).
+template <int P, bool BIG, bool REC, bool TRT = false>
+__global__ __launch_bounds__(256, 2) void k_step2_fused(
+    Pop<P> in, Pop<P> out, Coef<typename PrecT<P>::T> c, Geom g, int width, int nstrips,
+    int seg_len, typename PrecT<P>::T* rec0, typename PrecT<P>::T* rec1) {
+  using T = typename PrecT<P>::T;
+  constexpr int NT = 256;
+  __shared__ Fused2Lds<P, NT> L;
+  FusedCtx<P, BIG> k;
+  fused2_ctx(k, in, out, c, g, width, nstrips, seg_len, (int)threadIdx.x);
   Row<P> rb1[4];
   Row<MidP<P>::value> rb2[4];
   T nd1[2][NM], nd2[2][NM];
@@ -1163,6 +1121,261 @@ __global__ __launch_bounds__(256, Fused2Waves<P>::value) void k_step2_fused(
     fused2_iter<P, BIG, REC, 3, NT, TRT>(k, r0 + k.d * (it + 3), s, rb1, rb2, nd1, nd2, L, rec0,
                                  rec1);
     s = s == 2 ? 0 : s + 1;
+  }
+}
+
+// ------------------------------------- fused kernel, two steps a pass, FP64
+// The same pass with one set of four waves for each step: waves 0 to 3 run
+// A1..D1, waves 4 to 7 A2..D2, in the same phases between the same barriers
+// (the first step reaches the second through the ring of words only). The
+// LDS allows one workgroup per CU here, and with every wave running both
+// steps that was one wave per SIMD, whose dependent instructions and memory
+// operations nothing covered: 2048 x 8192 770 us a step, 585 split (4.3 TB/s
+// moved; a device copy reaches 5.0), 1001 x 2003 121 and 87. Each set's state
+// fits 256 registers because
+//  * f collides in phase C, with the pressure just formed (its collision
+//    needs no grad p), so that phase D needs only u and F of the node state
+//    and the second step's f leaves for memory in C;
+//  * f is loaded two rows behind g, for C, not with it.
+// A wave stands still while its memory operations queue for the address unit,
+// so they are spread over the phases, each batch behind the phase's own work:
+// g at the end of A, f at the end of C, into rows of their own that move to
+// the ones D frees (both at the top of A: 743 us; g in A, f in B: 602; both in
+// D: 830). The second step stores f in C and g in D (f in D: 629).
+struct SplitNode { double ux, uy, Fx, Fy; };
+
+// A recording replay must reproduce the plain steps bit for bit, and a sum of
+// two products, left to the compiler, was contracted one way in one variant of
+// this kernel and the other way in another: the sums here name their fused
+// multiply-adds, and a product whose value goes into sums is rounded first.
+__device__ __forceinline__ double rounded(double a, double b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+
+template <bool TRT>
+__device__ __forceinline__ void collide_f64(double f[9], const Macro<double>& m,
+                                            const Coef<double>& c) {
+  double gd[9] = {};
+  if constexpr (TRT) {
+    collide_node_trt(f, gd, m, 0.0, 0.0, c);
+  } else {
+    CollNode<double> n = coll_node(m, 0.0, 0.0);
+    n.dx = rounded(m.drx, 1.0 / 3.0);
+    n.dy = rounded(m.dry, 1.0 / 3.0);
+    n.ud = fmad(m.uy, n.dy, m.ux * n.dx);
+    collide_dirs(f, gd, n, coll_nodef(m, c), CollClass<double>{}, c, 1.0 - c.inv_tau_f,
+                 1.0 - c.inv_tau_g);
+  }
+}
+
+// Phase B of row b.
+template <int NT>
+__device__ __forceinline__ double split_mu(StageRings<double, NT>& S, int b, const Geom& g, int lc,
+                                           const Coef<double>& c) {
+  double v[3][3], gx, gy, lap;
+  lds3x3<double, NT>(S.phi, 3, b, g.ny, g.walls, lc, v);
+  stencil(v, gx, gy, lap);
+  const double mu = fmad(-c.kappa, lap, mu_bulk(v[1][1], c));
+  S.mu[b & 3][lc] = mu;
+  return mu;
+}
+
+// Phase C of row q: pressure into its ring, u and F into nd, and f (its
+// pulled populations on entry) collided.
+template <bool TRT, int NT>
+__device__ __forceinline__ void split_macro(StageRings<double, NT>& S, double f[9], int q,
+                                            const Geom& g, int lc, const Coef<double>& c,
+                                            SplitNode& nd, double rv[4]) {
+  double Sm, jx, jy, v[3][3], gphx, gphy, lapphi, gmux, gmuy, lapmu;
+  moments9(f, Sm, jx, jy);
+  lds3x3<double, NT>(S.phi, 3, q, g.ny, g.walls, lc, v);
+  stencil(v, gphx, gphy, lapphi);
+  const double ph = v[1][1];
+  lds3x3<double, NT>(S.mu, 3, q, g.ny, g.walls, lc, v);
+  stencil(v, gmux, gmuy, lapmu);
+  Macro<double> m;              // as macro_node
+  m.phi = ph;
+  m.mu = v[1][1];
+  m.rho = fmad(c.drho, ph, c.rho_B);
+  m.drx = c.drho * gphx;
+  m.dry = c.drho * gphy;
+  m.D = c.lam * lapmu;
+  const double dr = m.rho - c.rho_ref, inv = 3.0 * recip(m.rho);
+  m.Fx = fmad(-ph, gmux, dr * c.gx);
+  m.Fy = fmad(-ph, gmuy, dr * c.gy);
+  m.ux = rounded(fmad(m.Fx, 1.0 / 6.0, jx), inv);
+  m.uy = rounded(fmad(m.Fy, 1.0 / 6.0, jy), inv);
+  m.p = fmad(1.0 / 6.0, fmad(m.ux, m.drx, fmad(m.uy, m.dry, -(c.gamma * m.rho) * m.D)), Sm);
+  S.p[q & 3][lc] = m.p;
+  nd = {m.ux, m.uy, m.Fx, m.Fy};
+  rv[0] = m.p;
+  rv[1] = Sm;
+  rv[2] = jx;
+  rv[3] = jy;
+  collide_f64<TRT>(f, m, c);
+}
+
+// Phase D of row q: g collided.
+template <int NT>
+__device__ __forceinline__ void split_collide_g(const StageRings<double, NT>& S, int q,
+                                                const Geom& g, int lc, const Coef<double>& c,
+                                                const SplitNode& nd, double gg[9]) {
+  Macro<double> m = {};
+  m.phi = S.phi[q & 3][lc];
+  m.mu = S.mu[q & 3][lc];
+  m.rho = fmad(c.drho, m.phi, c.rho_B);
+  m.ux = nd.ux;
+  m.uy = nd.uy;
+  m.Fx = nd.Fx;
+  m.Fy = nd.Fy;
+  double v[3][3], dpx, dpy, lapp, fd[9] = {};
+  lds3x3<double, NT>(S.p, 3, q, g.ny, g.walls, lc, v);
+  stencil(v, dpx, dpy, lapp);
+  collide_node(fd, gg, m, dpx, dpy, c);
+}
+
+template <bool BIG, bool REC, int J, int NT, bool TRT>
+__device__ __forceinline__ void split_first(const FusedCtx<P_F64, BIG>& k, int r, int s,
+                                            double (&gb)[4][9], double (&fb)[2][9],
+                                            SplitNode (&nd)[2], Fused2Lds<P_F64, NT>& L,
+                                            double* rec) {
+  const Geom& g = k.g;
+  const int lc = k.lc, d = k.d;
+  double gn[9], fn[9], rv[4];
+  if (in_stage(k, r, 0)) {
+    const double ph = sum9(gb[J]);
+    L.s1.phi[r & 3][lc] = ph;
+    if constexpr (REC) record2(k, rec, 0, r, ph);
+  }
+  if (in_stage(k, r + d, 0)) pull_row<P_F64, BIG, true>(k, phys_row(r + d, g), gn);
+  __syncthreads();
+  if (in_stage(k, r - d, 1)) {
+    const double mu = split_mu<NT>(L.s1, r - d, g, lc, k.c);
+    if constexpr (REC) record2(k, rec, 1, r - d, mu);
+  }
+  __syncthreads();
+  if (in_stage(k, r - 2 * d, 2)) {
+    split_macro<TRT, NT>(L.s1, fb[J & 1], r - 2 * d, g, lc, k.c, nd[J & 1], rv);
+    if constexpr (REC) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) record2(k, rec, 2 + i, r - 2 * d, rv[i]);
+    }
+  }
+  if (in_stage(k, r - d, 2)) pull_row<P_F64, BIG, false>(k, phys_row(r - d, g), fn);
+  __syncthreads();
+  if (in_stage(k, r - 3 * d, 3)) {
+    double* const gg = gb[(J + 1) & 3];
+    split_collide_g<NT>(L.s1, r - 3 * d, g, lc, k.c, nd[(J + 1) & 1], gg);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+      L.mid.f[s][i][lc] = fb[(J + 1) & 1][i];
+      L.mid.g[s][i][lc] = gg[i];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    gb[(J + 1) & 3][i] = gn[i];
+    fb[(J + 1) & 1][i] = fn[i];
+  }
+  __syncthreads();
+}
+
+template <bool BIG, bool REC, int J, int NT, bool TRT>
+__device__ __forceinline__ void split_second(const FusedCtx<P_F64, BIG>& k, int r, int s,
+                                             double (&gb)[4][9], double (&fb)[4][9],
+                                             SplitNode (&nd)[2], Fused2Lds<P_F64, NT>& L,
+                                             double* rec) {
+  const Geom& g = k.g;
+  const int lc = k.lc, d = k.d;
+  const int r2 = r - 5 * d;
+  double rv[4];
+  if (in_stage(k, r2, 4)) {
+    // slots of rows r2 - 1, r2, r2 + 1, as in fused2_iter
+    const int s1 = s == 0 ? 2 : s - 1, s2 = s == 2 ? 0 : s + 1;
+    const int sl[3] = {d > 0 ? s : s1, s2, d > 0 ? s1 : s};
+    Row<P_F64> row;
+    pull_mid<P_F64, NT>(L.mid, sl, r2, g, lc, row);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+      gb[J][i] = row.g[i];
+      fb[J][i] = row.f[i];
+    }
+    const double ph = sum9(row.g);
+    L.s2.phi[r2 & 3][lc] = ph;
+    if constexpr (REC) record2(k, rec, 0, r2, ph);
+  }
+  __syncthreads();
+  if (in_stage(k, r2 - d, 5)) {
+    const double mu = split_mu<NT>(L.s2, r2 - d, g, lc, k.c);
+    if constexpr (REC) record2(k, rec, 1, r2 - d, mu);
+  }
+  __syncthreads();
+  {
+    const int q = r2 - 2 * d;
+    if (in_stage(k, q, 6)) {
+      double* const f = fb[(J + 2) & 3];
+      split_macro<TRT, NT>(L.s2, f, q, g, lc, k.c, nd[J & 1], rv);
+      if constexpr (REC) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) record2(k, rec, 2 + i, q, rv[i]);
+      }
+      if (in_stage(k, q, 7)) store_f<P_F64, BIG>(k, (uint32_t)(q * g.nx), f);
+    }
+  }
+  __syncthreads();
+  {
+    const int q = r2 - 3 * d;
+    if (in_stage(k, q, 7)) {
+      double* const gg = gb[(J + 1) & 3];
+      split_collide_g<NT>(L.s2, q, g, lc, k.c, nd[(J + 1) & 1], gg);
+      store_g<BIG>(k, (uint32_t)(q * g.nx), gg);
+    }
+  }
+  __syncthreads();
+}
+
+template <bool BIG, bool REC, bool TRT>
+__global__ __launch_bounds__(512, 2) void k_step2_split(Pop<P_F64> in, Pop<P_F64> out,
+                                                        Coef<double> c, Geom g, int width,
+                                                        int nstrips, int seg_len, double* rec0,
+                                                        double* rec1) {
+  constexpr int NT = 256;
+  __shared__ Fused2Lds<P_F64, NT> L;
+  FusedCtx<P_F64, BIG> k;
+  const int t = threadIdx.x & (NT - 1);
+  fused2_ctx(k, in, out, c, g, width, nstrips, seg_len, t);
+  const int r0 = k.d > 0 ? k.y0 - FH2 : k.y1 + FH2 - 1;
+  const int nit = (k.y1 - k.y0) + 2 * FH2 + 1;
+  int s = 0;   // ring slot D1 writes in this iteration: iteration index mod 3
+  double gb[4][9];
+  SplitNode nd[2];
+  // both sets run the same iterations, each with the same four barriers
+  if (__builtin_amdgcn_readfirstlane((int)threadIdx.x) < NT) {
+    double fb[2][9];
+    if (in_stage(k, r0, 0)) pull_row<P_F64, BIG, true>(k, phys_row(r0, g), gb[0]);
+    for (int it = 0; it < nit; it += 4) {
+      split_first<BIG, REC, 0, NT, TRT>(k, r0 + k.d * (it + 0), s, gb, fb, nd, L, rec0);
+      s = s == 2 ? 0 : s + 1;
+      split_first<BIG, REC, 1, NT, TRT>(k, r0 + k.d * (it + 1), s, gb, fb, nd, L, rec0);
+      s = s == 2 ? 0 : s + 1;
+      split_first<BIG, REC, 2, NT, TRT>(k, r0 + k.d * (it + 2), s, gb, fb, nd, L, rec0);
+      s = s == 2 ? 0 : s + 1;
+      split_first<BIG, REC, 3, NT, TRT>(k, r0 + k.d * (it + 3), s, gb, fb, nd, L, rec0);
+      s = s == 2 ? 0 : s + 1;
+    }
+  } else {
+    double fb[4][9];
+    for (int it = 0; it < nit; it += 4) {
+      split_second<BIG, REC, 0, NT, TRT>(k, r0 + k.d * (it + 0), s, gb, fb, nd, L, rec1);
+      s = s == 2 ? 0 : s + 1;
+      split_second<BIG, REC, 1, NT, TRT>(k, r0 + k.d * (it + 1), s, gb, fb, nd, L, rec1);
+      s = s == 2 ? 0 : s + 1;
+      split_second<BIG, REC, 2, NT, TRT>(k, r0 + k.d * (it + 2), s, gb, fb, nd, L, rec1);
+      s = s == 2 ? 0 : s + 1;
+      split_second<BIG, REC, 3, NT, TRT>(k, r0 + k.d * (it + 3), s, gb, fb, nd, L, rec1);
+      s = s == 2 ? 0 : s + 1;
+    }
   }
 }
 
@@ -1273,15 +1486,11 @@ FusedShape fused_shape(const Geom& g, int seg_rows, int resident) {
   return sh;
 }
 
-// FP64: also where a group spans more than 2 GiB, so that the two-step
-// kernel's stores beyond the range of a group descriptor (2 GiB past the
-// lane's offset) are dropped (the g_0 plane's descriptor is smaller still).
 template <int P>
 bool fused_big(const Geom& g) {
   const int64_t f_group = (P == P_F16 ? 1 : 9) * g.Ns * (int64_t)sizeof(typename BufT<P>::F);
   const int64_t g_group = (P == P_F32 ? 9 : 8) * g.Ns * (int64_t)sizeof(typename BufT<P>::GR);
-  const int64_t lim = P == P_F64 ? ((int64_t)1 << 31) : (int64_t)UINT32_MAX;
-  return f_group > lim || g_group > lim;
+  return f_group > (int64_t)UINT32_MAX || g_group > (int64_t)UINT32_MAX;
 }
 
 template <int P>
@@ -1353,9 +1562,14 @@ int fused2_resident() {
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_step2_fused<P, false, false>, 256, 0) !=
-      hipSuccess)
+  if constexpr (P == P_F64) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_step2_split<false, false, false>,
+                                                     512, 0) != hipSuccess)
+      return 0;
+  } else if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                 &per_cu, k_step2_fused<P, false, false>, 256, 0) != hipSuccess) {
     return 0;
+  }
   return cus * (per_cu > 0 ? per_cu : 1);
 }
 
@@ -1364,9 +1578,13 @@ static void launch_fused2_variant(const Pop<P>& i, const Pop<P>& o,
                                   const Coef<typename PrecT<P>::T>& c, const Geom& g,
                                   const FusedShape& sh, void* rec0, void* rec1, hipStream_t s) {
   using T = typename PrecT<P>::T;
-  hipLaunchKernelGGL((k_step2_fused<P, BIG, REC, TRT>), dim3(sh.nstrips * sh.nseg),
-                     dim3(sh.threads), 0, s, i, o, c, g, sh.width, sh.nstrips, sh.seg_rows,
-                     (T*)rec0, (T*)rec1);
+  const dim3 grid(sh.nstrips * sh.nseg);
+  if constexpr (P == P_F64)
+    hipLaunchKernelGGL((k_step2_split<BIG, REC, TRT>), grid, dim3(2 * sh.threads), 0, s, i, o, c, g,
+                       sh.width, sh.nstrips, sh.seg_rows, (T*)rec0, (T*)rec1);
+  else
+    hipLaunchKernelGGL((k_step2_fused<P, BIG, REC, TRT>), grid, dim3(sh.threads), 0, s, i, o, c, g,
+                       sh.width, sh.nstrips, sh.seg_rows, (T*)rec0, (T*)rec1);
 }
 
 template <int P>

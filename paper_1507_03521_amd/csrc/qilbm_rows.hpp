@@ -150,23 +150,19 @@ struct BufPop {
     else if constexpr (I == 0) return (int32_t)w;
     else return q_half(__builtin_bit_cast(__half, (uint16_t)(w >> 16)), I);
   }
-  // vb (stores): added to the lane's vector offset; 0x80000000 puts the
-  // store beyond a descriptor of at most 2 GiB, where the hardware drops it
   template <int I>
-  __device__ __forceinline__ void st_f(T v, uint32_t elem_row, uint32_t col,
-                                       uint32_t vb = 0) const {
+  __device__ __forceinline__ void st_f(T v, uint32_t elem_row, uint32_t col) const {
     F w;
     if constexpr (P == P_F16) w = __float2half_rn(v * H_SCALE(I));
     else w = v;
-    buf_st<F>(w, f_rsrc<I>(), col * (uint32_t)sizeof(F) + vb, f_soff<I>(elem_row));
+    buf_st<F>(w, f_rsrc<I>(), col * (uint32_t)sizeof(F), f_soff<I>(elem_row));
   }
   // stores g_I (I >= 1); returns its Q2.29 contribution in the fixed-point modes
   template <int I>
-  __device__ __forceinline__ int32_t st_g(T v, uint32_t elem_row, uint32_t col,
-                                          uint32_t vb = 0) const {
+  __device__ __forceinline__ int32_t st_g(T v, uint32_t elem_row, uint32_t col) const {
     const uint32_t so = g_soff<I>(elem_row);
     if constexpr (P == P_F64) {
-      buf_st<GR>(v, g_rsrc<I>(), col * (uint32_t)sizeof(GR) + vb, so);
+      buf_st<GR>(v, g_rsrc<I>(), col * (uint32_t)sizeof(GR), so);
       return 0;
     } else if constexpr (P == P_F32) {
       const int32_t q = __float2int_rn(v * GQ);
@@ -200,9 +196,8 @@ struct BufPop {
     const uint64_t w = (uint64_t)__builtin_bit_cast(uint32_t, fv) | ((uint64_t)(uint32_t)q << 32);
     buf_st<GR>(w, g_rsrc<I>(), col * (uint32_t)sizeof(GR), g_soff<I>(elem_row));
   }
-  __device__ __forceinline__ void st_g0(T v, int32_t q, uint32_t elem_row, uint32_t col,
-                                        uint32_t vb = 0) const {
-    if constexpr (P == P_F64) buf_st<G0>(v, rg0, col * (uint32_t)sizeof(G0) + vb, elem_row * (uint32_t)sizeof(G0));
+  __device__ __forceinline__ void st_g0(T v, int32_t q, uint32_t elem_row, uint32_t col) const {
+    if constexpr (P == P_F64) buf_st<G0>(v, rg0, col * (uint32_t)sizeof(G0), elem_row * (uint32_t)sizeof(G0));
     else buf_st<G0>(q, rg0, col * (uint32_t)sizeof(G0), elem_row * (uint32_t)sizeof(G0));
   }
 };

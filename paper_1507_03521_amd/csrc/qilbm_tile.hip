@@ -519,9 +519,8 @@ __global__ __launch_bounds__(256) void k_tile_mass(Pop<P> in, double* __restrict
 //   128 x 128    53.0 -> 4.27   35.2 -> 3.48   35.7 -> 4.52
 //   256 x 256    52.8 -> 6.01   35.4 -> 4.31   35.3 -> 4.99
 //   256 x 1024   53.1 -> 15.5   35.7 -> 9.0    36.1 -> 8.1
-//   701 x 1333   59.1 -> 68.4   38.2 -> 25.3   39.1 -> 21.8
-//   1001 x 2003   121 -> 182    53.1 -> 83.0   58.4 -> 43.7
-//   2048 x 2048   210 -> 317    91.6 -> 179     103 -> 116
+//   701 x 1333   42.1 -> 68.4   38.2 -> 25.3   39.1 -> 21.8
+//   1001 x 2003  86.8 -> 182    53.1 -> 83.0   58.4 -> 43.7
 // Two steps per launch pay while one round of workgroups covers the lattice:
 // launches and loads are halved, and the second collision of the halo runs on
 // compute units that would idle. The smallest tile that does it in one round
@@ -572,14 +571,14 @@ hipError_t launch_tile_variant(const void* pin, void* pout, const Coef<typename 
 // Tiles while both population buffers together stay within the 256 MB
 // Infinity Cache: a tile reads its halo again from L2 and beyond, which is
 // cheap only there. Past it the row sweep, which moves the state once per two
-// steps, is faster: fp64 at 934 k nodes (269 MB) 59 us against 61..68, at
-// 490 k (141 MB) 58 against 27; fp32 at 2.0 M nodes (289 MB) 53 against 69,
-// at 1.2 M (174 MB) 45 against 33; fp16 storage at 4.2 M nodes (319 MB) 103
-// against 116, at 2.0 M (152 MB) 58 against 44. The limit also keeps every
-// byte offset in a buffer below 2^31.
+// steps, is faster (us per step, row sweep against tiles): fp64 at 884 k nodes
+// (254 MB) 40.1 and 44.0, at 810 k 39.8 and 40.4, at 750 k 39.6 and 38.2, at 640 k
+// (184 MB) 39.4 and 33.1; fp32 at 2.0 M nodes (289 MB) 53 and 69, at 1.2 M (174 MB)
+// 45 and 33; fp16 storage at 4.2 M nodes (319 MB) 103 and 116, at 2.0 M (152 MB)
+// 58 and 44. The limit also keeps every byte offset in a buffer below 2^31.
 template <int P>
 bool tile_fits(const Geom& g) {
-  return 2 * pop_bytes(P, g.Ns) <= (int64_t)256 << 20;
+  return 2 * pop_bytes(P, g.Ns) <= (int64_t)(P == P_F64 ? 220 : 256) << 20;
 }
 
 template <int P>
