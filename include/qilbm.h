@@ -224,6 +224,18 @@ lbm_status lbm_step_record(lbm_ctx* ctx, void* record_dev);
  * nsteps < 0, a null array, or a null or misaligned record. Asynchronous. */
 lbm_status lbm_step_records(lbm_ctx* ctx, int64_t nsteps, void* const* records);
 
+/* One checkpoint segment without copies of the state: nsteps >= 1 steps as
+ * lbm_step (records NULL) or lbm_step_records, whose first launch reads the
+ * raw snapshot src_dev of time t in place of the context's state (NULL: the
+ * context's) and whose last one writes the state it ends in to dst_dev as a
+ * raw snapshot (its padding is left as it is) in place of the context (NULL:
+ * to the context). Both 256-byte aligned, lbm_state_bytes each, and different.
+ * After a segment into dst_dev the context holds no state: what reads or
+ * advances it returns LBM_ESTATE until lbm_load_raw, lbm_set_state or a
+ * segment from a snapshot into the context. Asynchronous. */
+lbm_status lbm_segment(lbm_ctx* ctx, const void* src_dev, int64_t t, int64_t nsteps,
+                       void* const* records, void* dst_dev);
+
 /* Raw snapshot of the internal state buffer in the storage precision
  * (lbm_state_bytes bytes): exact save/restore for checkpointing.
  * lbm_load_raw also sets the time counter to t. Asynchronous. */
@@ -301,6 +313,8 @@ lbm_status lbm_pass_info(const lbm_ctx* ctx, int32_t out[5]);
  * lbm_adjoint_step_record: the same step given the record of forward step
  *   t written by lbm_step_record (256-byte aligned); no forward
  *   recomputation. Asynchronous.
+ * lbm_adjoint_step_records: n such steps, from records[n - 1] down to
+ *   records[0] (a host array). Asynchronous.
  * lbm_adjoint_init: pulls the cotangent of s_0 back through the initial
  *   state map phi0 -> (f = 0, g = H_i(phi0, mu0)) given the same phi0_dev
  *   (FP64 [ny][nx], device) that lbm_init received: writes dL/dphi0 (FP64
@@ -318,6 +332,7 @@ lbm_status lbm_adjoint_begin(lbm_ctx* ctx, void* adj_workspace_dev,
 lbm_status lbm_adjoint_seed(lbm_ctx* ctx, const double* dL_dphi_dev);
 lbm_status lbm_adjoint_step(lbm_ctx* ctx, const void* fwd_state_dev);
 lbm_status lbm_adjoint_step_record(lbm_ctx* ctx, const void* record_dev);
+lbm_status lbm_adjoint_step_records(lbm_ctx* ctx, int64_t n, void* const* records);
 lbm_status lbm_adjoint_init(lbm_ctx* ctx, const double* phi0_dev, double* dL_dphi0_dev,
                             double out[2]);
 

@@ -64,12 +64,15 @@ SIGNATURES = {
     "lbm_launch_info": (c_int32, [c_void_p, POINTER(c_int32)]),
     "lbm_set_pass": (c_int32, [c_void_p, c_int32, c_int32]),
     "lbm_step_records": (c_int32, [c_void_p, c_int64, POINTER(c_void_p)]),
+    "lbm_segment": (c_int32, [c_void_p, c_void_p, c_int64, c_int64, POINTER(c_void_p),
+                              c_void_p]),
     "lbm_pass_info": (c_int32, [c_void_p, POINTER(c_int32)]),
     "lbm_adjoint_workspace_bytes": (c_size_t, [_P]),
     "lbm_adjoint_begin": (c_int32, [c_void_p, c_void_p, c_size_t, c_void_p]),
     "lbm_adjoint_seed": (c_int32, [c_void_p, c_void_p]),
     "lbm_adjoint_step": (c_int32, [c_void_p, c_void_p]),
     "lbm_adjoint_step_record": (c_int32, [c_void_p, c_void_p]),
+    "lbm_adjoint_step_records": (c_int32, [c_void_p, c_int64, POINTER(c_void_p)]),
     "lbm_adjoint_init": (c_int32, [c_void_p, c_void_p, c_void_p, _D]),
     "lbm_adjoint_set": (c_int32, [c_void_p, c_void_p, c_void_p]),
     "lbm_adjoint_get": (c_int32, [c_void_p, c_void_p, c_void_p, _D]),

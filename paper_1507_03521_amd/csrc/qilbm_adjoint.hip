@@ -1256,6 +1256,22 @@ lbm_status lbm_adjoint_step_record(lbm_ctx* ctx, const void* record_dev) {
   return adj_core<float>(v, (const float*)record_dev);
 }
 
+lbm_status lbm_adjoint_step_records(lbm_ctx* ctx, int64_t n, void* const* records) {
+  if (!ctx || n < 0 || (n > 0 && !records)) return LBM_EINVAL;
+  for (int64_t k = 0; k < n; ++k)
+    if (!records[k] || (uintptr_t)records[k] % ALIGN != 0) return LBM_EINVAL;
+  CtxView v = ctx_view(ctx);
+  if (v.prm->trt_magic > 0.0) return LBM_EINVAL;
+  if (!v.adj->active) return LBM_ESTATE;
+  for (int64_t k = n - 1; k >= 0; --k) {
+    const lbm_status s = v.prm->precision == LBM_FP64
+                             ? adj_core<double>(v, (const double*)records[k])
+                             : adj_core<float>(v, (const float*)records[k]);
+    if (s != LBM_OK) return s;
+  }
+  return LBM_OK;
+}
+
 lbm_status lbm_adjoint_init(lbm_ctx* ctx, const double* phi0, double* dphi0, double out[2]) {
   if (!ctx || !phi0 || !dphi0 || !out) return LBM_EINVAL;
   CtxView v = ctx_view(ctx);

@@ -26,6 +26,7 @@ struct lbm_ctx {
   int nred;
   double* red_out;    // 8 doubles
   int64_t t;
+  bool held;          // pop[cur] holds the state (false after lbm_segment into a snapshot)
   int seg_rows;
   int resident;       // fused workgroups resident at once on this device
   int pass_steps;     // time steps per pass of the fused kernel (1 or 2)
@@ -151,9 +152,12 @@ char* p_f(lbm_ctx* c) { return c->fields + 2 * c->geom.Ns * 8; }
 // n steps; with recs not null, step k also writes the record of the state it
 // starts from into recs[k] (planes phi, mu, p, S, jx, jy of the compute type
 // at stride Ns). Pairs of steps run as one two-step launch when the context
-// uses two steps per pass (a pair's records come from that launch).
+// uses two steps per pass (a pair's records come from that launch). With src
+// not null the first launch reads the raw state src in place of the context's;
+// with dst not null the last one writes the raw state dst in its place.
 template <int P>
-lbm_status step_p(lbm_ctx* c, int64_t n, void* const* recs) {
+lbm_status step_p(lbm_ctx* c, int64_t n, void* const* recs, const char* src = nullptr,
+                  char* dst = nullptr) {
   using T = typename PrecT<P>::T;
   const Coef<T> k = coef_t<T>(c);
   const bool unfused = c->prm.flags & LBM_FLAG_UNFUSED;
@@ -161,6 +165,15 @@ lbm_status step_p(lbm_ctx* c, int64_t n, void* const* recs) {
   if (trt && recs) return LBM_EINVAL;
   const int64_t pl = c->geom.Ns;
   int64_t done = 0;
+  const auto in = [&] { return done == 0 && src ? src : c->pop[c->cur]; };
+  const auto out = [&](int steps) {
+    return dst && done + steps == n ? dst : c->pop[c->cur ^ 1];
+  };
+  const auto taken = [&](int steps) {
+    done += steps;
+    c->cur ^= 1;
+    c->t += steps;
+  };
   // small lattices run as tiles, unless the caller has set the rows per
   // segment of the row-sweeping kernel that would run otherwise
   const bool small = !unfused && tile_fits<P>(c->geom);
@@ -168,55 +181,49 @@ lbm_status step_p(lbm_ctx* c, int64_t n, void* const* recs) {
   if constexpr (P != P_F16) {
     const bool tile2 = small && c->pass_steps == 2 && c->pass_seg_rows == 0;
     if (tile2 && tile_steps<P>(c->geom) == 2) {
-      for (; n - done >= 2; done += 2) {
-        if (launch_step2_tile<P>(c->pop[c->cur], c->pop[c->cur ^ 1], k, c->geom,
-                                 recs ? recs[done] : nullptr, recs ? recs[done + 1] : nullptr,
-                                 c->stream, trt) != hipSuccess)
+      while (n - done >= 2) {
+        if (launch_step2_tile<P>(in(), out(2), k, c->geom, recs ? recs[done] : nullptr,
+                                 recs ? recs[done + 1] : nullptr, c->stream, trt) != hipSuccess)
           return LBM_EDEVICE;
-        c->cur ^= 1;
-        c->t += 2;
+        taken(2);
       }
     } else if (tile2) {
       // a pair of steps is two launches
-      for (; done < n / 2 * 2; ++done) {
-        if (launch_step_tile<P>(c->pop[c->cur], c->pop[c->cur ^ 1], k, c->geom,
-                                recs ? recs[done] : nullptr, c->stream, trt) != hipSuccess)
+      while (done < n / 2 * 2) {
+        if (launch_step_tile<P>(in(), out(1), k, c->geom, recs ? recs[done] : nullptr, c->stream,
+                                trt) != hipSuccess)
           return LBM_EDEVICE;
-        c->cur ^= 1;
-        c->t += 1;
+        taken(1);
       }
     }
   }
   if (!unfused && c->pass_steps == 2 && n - done >= 2) {
     const FusedShape sh2 = fused2_shape<P>(c->geom, c->pass_seg_rows, c->resident2);
-    for (; n - done >= 2; done += 2) {
+    while (n - done >= 2) {
       void* r0 = recs ? recs[done] : nullptr;
       void* r1 = recs ? recs[done + 1] : nullptr;
-      if (launch_step2_fused<P>(c->pop[c->cur], c->pop[c->cur ^ 1], k, c->geom, sh2, r0, r1,
-                                c->stream, trt) != hipSuccess)
+      if (launch_step2_fused<P>(in(), out(2), k, c->geom, sh2, r0, r1, c->stream, trt) !=
+          hipSuccess)
         return LBM_EDEVICE;
-      c->cur ^= 1;
-      c->t += 2;
+      taken(2);
     }
   }
   const FusedShape sh = fused_shape<P>(c->geom, c->seg_rows, c->resident);
-  for (; done < n; ++done) {
+  while (done < n) {
     void* rec = recs ? recs[done] : nullptr;
     hipError_t e;
     if (unfused && rec)
-      e = launch_step_unfused<P>(c->pop[c->cur], c->pop[c->cur ^ 1], (T*)rec, (T*)rec + pl,
-                                 (T*)rec + 2 * pl, (T*)rec + 3 * pl, k, c->geom, c->stream);
+      e = launch_step_unfused<P>(in(), out(1), (T*)rec, (T*)rec + pl, (T*)rec + 2 * pl,
+                                 (T*)rec + 3 * pl, k, c->geom, c->stream);
     else if (unfused)
-      e = launch_step_unfused<P>(c->pop[c->cur], c->pop[c->cur ^ 1], phi_f(c), mu_f(c), p_f(c),
-                                 nullptr, k, c->geom, c->stream, trt);
+      e = launch_step_unfused<P>(in(), out(1), phi_f(c), mu_f(c), p_f(c), nullptr, k, c->geom,
+                                 c->stream, trt);
     else if (tile1)
-      e = launch_step_tile<P>(c->pop[c->cur], c->pop[c->cur ^ 1], k, c->geom, rec, c->stream, trt);
+      e = launch_step_tile<P>(in(), out(1), k, c->geom, rec, c->stream, trt);
     else
-      e = launch_step_fused<P>(c->pop[c->cur], c->pop[c->cur ^ 1], k, c->geom, sh, rec,
-                               c->stream, trt);
+      e = launch_step_fused<P>(in(), out(1), k, c->geom, sh, rec, c->stream, trt);
     if (e != hipSuccess) return LBM_EDEVICE;
-    c->cur ^= 1;
-    c->t += 1;
+    taken(1);
   }
   return LBM_OK;
 }
@@ -343,6 +350,7 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* params, void* workspace_dev
   c->nred = L.nred;
   c->red_out = (double*)(c->ws + L.red);
   c->t = 0;
+  c->held = true;
   c->seg_rows = 0;
   c->resident = QILBM_DISPATCH(params->precision, fused_resident);
   // two steps per pass where it is the faster kernel (FP32, FP64); FP16
@@ -353,9 +361,11 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* params, void* workspace_dev
   c->resident2 = QILBM_DISPATCH(params->precision, fused2_resident);
   c->pbytes = pop_bytes(params->precision, c->geom.Ns);
   Coef<double> k = coef_t<double>(c);
-  // both population buffers start zeroed, padding included, so that raw
-  // snapshots of equal states are equal byte for byte
-  hipError_t e = launch_zero(c->ws + L.pop0, L.fields - L.pop0, c->stream);
+  // the padding of both population buffers starts zeroed, so that raw
+  // snapshots of equal states are equal byte for byte (the planes themselves
+  // are written whole, by launch_init and by the steps)
+  hipError_t e = QILBM_DISPATCH(params->precision, launch_zero_padding, c->pop[0], c->pop[1],
+                                c->geom, c->stream);
   if (e == hipSuccess)
     e = QILBM_DISPATCH(params->precision, launch_init, phi0_dev, c->pop[0], k, c->geom,
                        c->stream);
@@ -369,6 +379,7 @@ lbm_status lbm_init(lbm_ctx** out, const lbm_params* params, void* workspace_dev
 
 lbm_status lbm_step(lbm_ctx* c, int64_t nsteps) {
   if (!c || nsteps < 0) return LBM_EINVAL;
+  if (!c->held) return LBM_ESTATE;
   return QILBM_DISPATCH(c->prm.precision, step_p, c, nsteps, (void* const*)nullptr);
 }
 
@@ -380,6 +391,7 @@ size_t lbm_record_bytes(const lbm_ctx* c) {
 lbm_status lbm_step_record(lbm_ctx* c, void* record_dev) {
   if (!c || !record_dev || trt_of(c)) return LBM_EINVAL;
   if ((uintptr_t)record_dev % ALIGN != 0) return LBM_EINVAL;
+  if (!c->held) return LBM_ESTATE;
   void* const recs[1] = {record_dev};
   return QILBM_DISPATCH(c->prm.precision, step_p, c, 1, recs);
 }
@@ -388,12 +400,30 @@ lbm_status lbm_step_records(lbm_ctx* c, int64_t nsteps, void* const* records) {
   if (!c || nsteps < 0 || (nsteps > 0 && !records) || trt_of(c)) return LBM_EINVAL;
   for (int64_t k = 0; k < nsteps; ++k)
     if (!records[k] || (uintptr_t)records[k] % ALIGN != 0) return LBM_EINVAL;
+  if (!c->held) return LBM_ESTATE;
   return QILBM_DISPATCH(c->prm.precision, step_p, c, nsteps, records);
+}
+
+lbm_status lbm_segment(lbm_ctx* c, const void* src, int64_t t, int64_t nsteps,
+                       void* const* records, void* dst) {
+  if (!c || nsteps < 1 || (src && t < 0) || (records && trt_of(c))) return LBM_EINVAL;
+  if ((uintptr_t)src % ALIGN != 0 || (uintptr_t)dst % ALIGN != 0) return LBM_EINVAL;
+  if (src && src == dst) return LBM_EINVAL;
+  if (records)
+    for (int64_t k = 0; k < nsteps; ++k)
+      if (!records[k] || (uintptr_t)records[k] % ALIGN != 0) return LBM_EINVAL;
+  if (!src && !c->held) return LBM_ESTATE;
+  if (src) c->t = t;
+  const lbm_status s = QILBM_DISPATCH(c->prm.precision, step_p, c, nsteps, records,
+                                      (const char*)src, (char*)dst);
+  c->held = s == LBM_OK && !dst;
+  return s;
 }
 
 lbm_status lbm_moments(lbm_ctx* c, double* phi, double* rho, double* ux, double* uy, double* p,
                        double* mu) {
   if (!c) return LBM_EINVAL;
+  if (!c->held) return LBM_ESTATE;
   MomentOut mo;
   mo.phi = phi;
   mo.rho = rho;
@@ -406,6 +436,7 @@ lbm_status lbm_moments(lbm_ctx* c, double* phi, double* rho, double* ux, double*
 
 lbm_status lbm_mass(lbm_ctx* c, double out[4]) {
   if (!c || !out) return LBM_EINVAL;
+  if (!c->held) return LBM_ESTATE;
   lbm_status s = QILBM_DISPATCH(c->prm.precision, mass_p, c);
   if (s != LBM_OK) return s;
   if (hipMemcpyAsync(out, c->red_out, 4 * sizeof(double), hipMemcpyDeviceToHost, c->stream) !=
@@ -431,12 +462,14 @@ lbm_status lbm_mass_noalloc(const lbm_params* params, const void* state_dev, dou
 
 lbm_status lbm_get_state(lbm_ctx* c, double* f, double* g) {
   if (!c || !f || !g) return LBM_EINVAL;
+  if (!c->held) return LBM_ESTATE;
   return st(QILBM_DISPATCH(c->prm.precision, launch_to_canonical, c->pop[c->cur], f, g, c->geom,
                            c->stream));
 }
 
 lbm_status lbm_set_state(lbm_ctx* c, const double* f, const double* g) {
   if (!c || !f || !g) return LBM_EINVAL;
+  c->held = true;
   return st(QILBM_DISPATCH(c->prm.precision, launch_from_canonical, f, g, c->pop[c->cur], c->geom,
                            c->stream));
 }
@@ -445,12 +478,14 @@ size_t lbm_state_bytes(const lbm_ctx* c) { return c ? (size_t)c->pbytes : 0; }
 
 lbm_status lbm_save_raw(lbm_ctx* c, void* dst) {
   if (!c || !dst) return LBM_EINVAL;
+  if (!c->held) return LBM_ESTATE;
   return st(hipMemcpyAsync(dst, c->pop[c->cur], c->pbytes, hipMemcpyDeviceToDevice, c->stream));
 }
 
 lbm_status lbm_load_raw(lbm_ctx* c, const void* src, int64_t t) {
   if (!c || !src || t < 0) return LBM_EINVAL;
   c->t = t;
+  c->held = true;
   return st(hipMemcpyAsync(c->pop[c->cur], src, c->pbytes, hipMemcpyDeviceToDevice, c->stream));
 }
 

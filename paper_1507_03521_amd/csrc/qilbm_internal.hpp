@@ -49,6 +49,9 @@ bool fused_big(const Geom& g);
 // kernel (no memset node, so the call may sit in a captured graph).
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
 
+// Zeroes what two population buffers hold beyond their planes' N elements.
+template <int P>
+hipError_t launch_zero_padding(void* pop0, void* pop1, const Geom& g, hipStream_t s);
 template <int P>
 hipError_t launch_init(const double* phi0, void* pop, const Coef<double>& c, const Geom& g,
                        hipStream_t s);

@@ -1395,6 +1395,36 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The Ns - N elements behind each plane (block x: plane, y: buffer), in
+// 2-byte units, and the last plane's rest up to a multiple of 256 bytes.
+template <int P>
+__global__ __launch_bounds__(256) void k_zero_padding(Pop<P> a, Pop<P> b, Geom g) {
+  char* const base = blockIdx.y ? b.base : a.base;
+  const int64_t Ns = g.Ns;
+  const int k = blockIdx.x;
+  int64_t off, es;                // the plane's byte offset and element size
+  if constexpr (P == P_F16) {
+    off = k == 0 ? 0 : (k == 1 ? 2 * Ns : 6 * Ns + (k - 2) * 4 * Ns);
+    es = k == 0 ? 2 : 4;
+  } else {
+    off = k * 8 * Ns;
+    es = 8;
+  }
+  const int64_t total = pop_bytes(P, Ns);
+  int64_t end = off + Ns * es;
+  if (end == total) end = (total + 255) / 256 * 256;
+  for (int64_t i = off + g.N * es + 2 * threadIdx.x; i < end; i += 512)
+    *reinterpret_cast<uint16_t*>(base + i) = 0;
+}
+
+template <int P>
+hipError_t launch_zero_padding(void* pop0, void* pop1, const Geom& g, hipStream_t s) {
+  constexpr int planes = P == P_F64 ? 18 : (P == P_F32 ? 9 : 10);
+  hipLaunchKernelGGL(k_zero_padding<P>, dim3(planes, 2), dim3(256), 0, s,
+                     Pop<P>{(char*)pop0, g.Ns}, Pop<P>{(char*)pop1, g.Ns}, g);
+  return hipGetLastError();
+}
+
 template <int P>
 hipError_t launch_init(const double* phi0, void* pop, const Coef<double>& c, const Geom& g,
                        hipStream_t s) {
@@ -1633,6 +1663,7 @@ hipError_t launch_sum_partials(const double* part, int nb, int width, double* ou
 }
 
 #define QILBM_INSTANTIATE(P)                                                                     \
+  template hipError_t launch_zero_padding<P>(void*, void*, const Geom&, hipStream_t);            \
   template hipError_t launch_init<P>(const double*, void*, const Coef<double>&, const Geom&,     \
                                      hipStream_t);                                               \
   template hipError_t launch_from_canonical<P>(const double*, const double*, void*, const Geom&, \

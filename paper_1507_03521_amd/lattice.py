@@ -133,9 +133,12 @@ class Lattice:
     def state_bytes(self) -> int:
         return int(self.lib.lbm_state_bytes(self.ctx))
 
+    def empty_raw(self) -> torch.Tensor:
+        return torch.empty(self.state_bytes, dtype=torch.uint8, device=self.device)
+
     def save_raw(self, out: torch.Tensor | None = None) -> torch.Tensor:
         if out is None:
-            out = torch.empty(self.state_bytes, dtype=torch.uint8, device=self.device)
+            out = self.empty_raw()
         assert out.numel() >= self.state_bytes and out.is_contiguous()
         _lib.check(self.lib.lbm_save_raw(self.ctx, _ptr(out)), "lbm_save_raw")
         return out
@@ -155,10 +158,36 @@ class Lattice:
     def step_records(self, records) -> None:
         """len(records) steps, writing the record of the state step k starts
         from into records[k] (uint8 device tensors of record_bytes each)."""
+        _lib.check(self.lib.lbm_step_records(self.ctx, len(records), self.record_array(records)),
+                   "lbm_step_records")
+
+    def record_array(self, records):
+        """The pointers of records (uint8 device tensors of record_bytes each) as
+        the library takes them; the caller keeps the tensors."""
+        nbytes = self.record_bytes
         for r in records:
-            assert r.numel() >= self.record_bytes and r.is_contiguous()
-        arr = (c_void_p * max(len(records), 1))(*[_ptr(r) for r in records])
-        _lib.check(self.lib.lbm_step_records(self.ctx, len(records), arr), "lbm_step_records")
+            assert r.numel() >= nbytes and r.is_contiguous()
+        return (c_void_p * max(len(records), 1))(*[_ptr(r) for r in records])
+
+    def segment(self, n: int, src: torch.Tensor | None = None, t: int = 0, records=None,
+                dst: torch.Tensor | None = None) -> None:
+        """n steps from the raw snapshot ``src`` of time ``t`` (None: from the
+        lattice's state), into the raw snapshot ``dst`` (None: the lattice),
+        without a copy of either. ``records``: a :meth:`record_array` of at
+        least n to write, or None. After a segment into ``dst`` the lattice
+        holds no state until it is loaded."""
+        for x in (src, dst):
+            assert x is None or (x.numel() >= self.state_bytes and x.is_contiguous())
+        assert records is None or len(records) >= n
+        _lib.check(self.lib.lbm_segment(self.ctx, None if src is None else _ptr(src), int(t),
+                                        int(n), records, None if dst is None else _ptr(dst)),
+                   "lbm_segment")
+
+    def adjoint_step_records(self, records, n: int) -> None:
+        """Adjoint steps of records n - 1 down to 0 of a :meth:`record_array`."""
+        assert len(records) >= n
+        _lib.check(self.lib.lbm_adjoint_step_records(self.ctx, int(n), records),
+                   "lbm_adjoint_step_records")
 
     def set_pass(self, steps: int, seg_rows: int = 0) -> None:
         """Time steps per fused launch in step() (2: temporal blocking, the
