@@ -252,8 +252,12 @@ __device__ __forceinline__ void adj_tile(__amdgpu_buffer_rsrc_t rrec, __amdgpu_b
   }
 }
 
+// FP64: held to the 168 registers that three wavefronts per SIMD allow (192
+// left to itself, nothing spilled: 512 x 512 38.1 us a step, 31.2 held; four
+// wavefronts spill: 68.7). FP32 takes 92 to 102 by itself (80: 27.4 us
+// against 20.6).
 template <typename T, int TX, int TY, int NT>
-__global__ __launch_bounds__(NT) void k_adj_tile(const T* __restrict__ rec,
+__global__ __launch_bounds__(NT, sizeof(T) == 8 ? 3 : 1) void k_adj_tile(const T* __restrict__ rec,
                                                  const T* __restrict__ hin, T* __restrict__ hout,
                                                  double* acc_part, Coef<T> c, Geom g, int ntx) {
   __shared__ AdjTileLds<T, (TX + 8) * (TY + 8)> L;
@@ -284,8 +288,8 @@ hipError_t launch(const void* rec, const void* hin, void* hout, double* part, co
 // units, so that small lattices spread over all of them (fp64 64 x 64: 8 x 4
 // 7.0 us, 16 x 4 7.3, 32 x 8 9.4; 128 x 128: 8.6, 7.6, 9.7; 256 x 256: 25.7,
 // 16.3, 10.8). Beyond one round FP32 keeps 32 x 8 (512 x 512: 20.3 us; 16 x 8
-// 20.7, 16 x 4 30.5); FP64, whose 207 registers leave two wavefronts per SIMD,
-// takes 16 x 8 (36.3 us; 32 x 8 39.0).
+// 20.7, 16 x 4 30.5) and FP64 takes 16 x 8 (31.2 us; 24 x 8 47.5, 12 x 8 36.4,
+// 16 x 4 42.7).
 enum Shape { T8x4, T16x4, T32x8, T16x8 };
 template <typename T>
 Shape shape(const Geom& g) {
@@ -296,14 +300,14 @@ Shape shape(const Geom& g) {
 
 }  // namespace
 
-// While both cotangent buffers and the record fit in the 256 MB Infinity
-// Cache (as the forward tiles, whose limit this is): fp64 490 k nodes (165 MB)
-// 66 us against the row sweep's 127, 934 k (314 MB) 155 against 129; fp32
-// 934 k (157 MB) 60 against 83, 2.0 M (337 MB) 159 against 122. It also
-// keeps the byte offsets in a buffer below 2^31.
+// While both cotangent buffers and the record are about what the 256 MB
+// Infinity Cache holds (us per step, tiles against the row sweep): fp64 490 k
+// nodes (165 MB) 54 and 127, 810 k (272 MB) 92 and 130, 1.0 M (336 MB) 136 and 158,
+// 1.2 M (407 MB) 177 and 169; fp32 934 k (157 MB) 60 and 83, 2.0 M (337 MB) 159 and
+// 122. It also keeps the byte offsets in a buffer below 2^31.
 template <typename T>
 bool adj_tile_fits(const Geom& g) {
-  return (2 * 18 + 6) * g.Ns * (int64_t)sizeof(T) <= (int64_t)256 << 20;
+  return (2 * 18 + 6) * g.Ns * (int64_t)sizeof(T) <= (int64_t)(sizeof(T) == 8 ? 325 : 256) << 20;
 }
 
 template <typename T>

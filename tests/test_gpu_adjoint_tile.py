@@ -29,7 +29,8 @@ UNFUSED = 2
     (9, 5, wl.WALLS_Y, "fp64"), (64, 128, wl.WALLS_Y, "fp64"), (65, 128, wl.PERIODIC, "fp32"),
     (129, 65, wl.WALLS_Y, "fp64"), (128, 128, wl.WALLS_Y, "fp32"), (129, 129, wl.WALLS_Y, "fp64"),
     (256, 256, wl.PERIODIC, "fp64"), (257, 257, wl.WALLS_Y, "fp64"), (257, 255, wl.WALLS_Y, "fp32"),
-    (892, 892, wl.WALLS_Y, "fp64"), (895, 893, wl.WALLS_Y, "fp64")])
+    (892, 892, wl.WALLS_Y, "fp64"), (895, 893, wl.WALLS_Y, "fp64"), (1005, 1007, wl.WALLS_Y, "fp64"),
+    (1009, 1009, wl.PERIODIC, "fp64")])
 def test_tiled_adjoint_matches_three_kernels(nx, ny, bc, precision):
     from paper_1507_03521_amd import Lattice
     print(f"case adjoint tiles {nx}x{ny} bc={bc} {precision}", flush=True)
