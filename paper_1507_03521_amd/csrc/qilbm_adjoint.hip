@@ -847,11 +847,11 @@ __device__ __forceinline__ void adj_iter(const AdjCtx<T, BIG>& k, int r, AdjLds<
   // The loads for the next iteration go out as soon as their registers are
   // free: a wait on the memory counter also waits for every store issued
   // before the load it needs, so a load issued behind the stores of D'
-  // would wait for them. hf and hg are free once A' has kept what it needs.
-  if (k.in(r, 1)) {
-    gather_post<T>(k, r, 0, hf);
-    gather_post<T>(k, r, 9, hg);
-  }
+  // would wait for them. hf and hg are free once A' has kept what it needs; hf
+  // follows at the end of B', so that the 18 do not queue for the address
+  // unit in one place while the wave stands still (2048 x 4096 FP32 406 us,
+  // 384; 2048 x 2048 FP64 464, 459; both at the end of C' or B' no gain).
+  if (k.in(r, 1)) gather_post<T>(k, r, 9, hg);
   __syncthreads();
   // B': pressure cotangent and the macroscopic transposes of row b
   T o_S = T(0), o_jx = T(0), o_jy = T(0);
@@ -900,6 +900,7 @@ __device__ __forceinline__ void adj_iter(const AdjCtx<T, BIG>& k, int r, AdjLds<
     fbar_out([&](int i, T v) { k.hout.st_if(ok, i, ro, (uint32_t)k.x, (uint32_t)g.nx, v); },
              fdr[(J + 1) & 1], o_S, o_jx, o_jy);
   }
+  if (k.in(r, 1)) gather_post<T>(k, r, 0, hf);
   __syncthreads();
   T he[9] = {};
   if constexpr (!KeepGd<T>::value)
