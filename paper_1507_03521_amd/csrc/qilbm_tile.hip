@@ -97,6 +97,16 @@ __device__ __forceinline__ void tile_load_g(__amdgpu_buffer_rsrc_t rs, uint32_t 
   }
 }
 
+// FP64: a node's f.
+template <bool EDGE, int I = 0>
+__device__ __forceinline__ void tile_load_f(__amdgpu_buffer_rsrc_t rs, uint32_t Ns,
+                                            const TileNode& k, double f[9]) {
+  if constexpr (I < 9) {
+    f[I] = tile_pull<double, P_F64, false, EDGE, I>(rs, Ns, k);
+    tile_load_f<EDGE, I + 1>(rs, Ns, k, f);
+  }
+}
+
 template <int P, int I = 0>
 __device__ __forceinline__ int32_t g_words_q(const typename GWord<P>::T w[9]) {
   if constexpr (I < 9) {
@@ -211,6 +221,12 @@ __device__ __forceinline__ void tile_phase(__amdgpu_buffer_rsrc_t rin, __amdgpu_
   constexpr int NPHI = frame_count<IX + 2, IY + 2, 2>(), NMU = frame_count<IX + 2, IY + 2, 1>();
   constexpr int MW = IX + 8;          // pitch of M when FROM_MID
   static_assert(NP <= NT, "one own node per thread");
+  // FP64, whose f has words of its own, loads it behind A's barrier where a
+  // launch is one round of workgroups (two steps: 64 x 64 3.6 us a step, 3.45;
+  // 256 x 256 6.1, 5.75): C is the first to need it, and ahead of the barrier it
+  // kept phi waiting. With more workgroups to switch to, ahead is better
+  // (512 x 512 15.2, 15.5).
+  constexpr bool F_LATE = P == P_F64 && TO_MID;
   const int t = threadIdx.x;
   const uint32_t Ns = (uint32_t)g.Ns;
   const int slot = t >= NP ? t - NP : t + NT - NP;
@@ -233,6 +249,7 @@ __device__ __forceinline__ void tile_phase(__amdgpu_buffer_rsrc_t rin, __amdgpu_
   // A
   if (t < NP) {
     if constexpr (FROM_MID) mid_row<P, MW, NM_, EDGE>(M, (ly + 4) * MW + lx + 4, k.lo, k.hi, row);
+    else if constexpr (F_LATE) tile_load_g<P, EDGE>(rin, Ns, k, row.g);
     else tile_load_dirs<P, EDGE>(rin, Ns, k, row);
   }
   for (int h = slot; h < NPHI; h += NT) {
@@ -251,6 +268,8 @@ __device__ __forceinline__ void tile_phase(__amdgpu_buffer_rsrc_t rin, __amdgpu_
     L.phi[e] = ph;
   }
   __syncthreads();
+  if constexpr (F_LATE)
+    if (t < NP) tile_load_f<EDGE>(rin, Ns, k, row.f);
   // B
   T mu = T(0);
   if (t < NP) {
