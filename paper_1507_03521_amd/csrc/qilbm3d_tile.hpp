@@ -7,8 +7,8 @@
 // the z-sweep kernel has too few columns for): k3_tile_phi, k3_tile_f (mu, the
 // pressure and f's collision), k3_tile_g. Each population set is pulled once
 // for its collision, g once more for phi. Bound by memory (the Infinity Cache
-// up to about 64^3 in FP64) at some 870 bytes a node in FP64: 64^3 44 us,
-// 256^3 3.06 ms = 4.8 TB/s. The row-wave kernels that it replaces, which
+// up to about 64^3 in FP64) at some 900 bytes a node in FP64: 64^3 44 us,
+// 256^3 2.91 ms = 5.2 TB/s. The row-wave kernels that it replaces, which
 // gathered every stencil through L1 and formed mu in a launch of its own,
 // took 80 us and 3.17 ms, and 51 us against 16 at 32^3: there the mu launch
 // was eight workgroups, 36 us.
