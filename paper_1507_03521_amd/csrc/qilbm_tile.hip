@@ -125,6 +125,26 @@ __device__ __forceinline__ typename PrecT<P>::T g_words_phi(const typename GWord
   else return T(g_words_q<P>(w)) * T(GQI);
 }
 
+// phi as the moments and totals take it: the rounded sum of the stored values.
+// FP16 storage sums its halves exactly (binary64), not as the truncated Q2.29
+// contributions that a step conserves, which are up to 1.5e-8 below them.
+template <int P, int I = 0>
+__device__ __forceinline__ double g_words_sum(const typename GWord<P>::T w[9]) {
+  if constexpr (I < 9) {
+    double v;
+    if constexpr (I == 0) v = double((int32_t)w[0]) * GQI_D;
+    else v = double(BufPop<P>::template val_g<I>(w[I]));
+    return v + g_words_sum<P, I + 1>(w);
+  } else {
+    return 0.0;
+  }
+}
+template <int P>
+__device__ __forceinline__ typename PrecT<P>::T moment_phi(const typename GWord<P>::T w[9]) {
+  if constexpr (P == P_F16) return float(g_words_sum<P>(w));
+  else return g_words_phi<P>(w);
+}
+
 // Stores a node's words at element n.
 template <int P, int POL, int I = 0>
 __device__ __forceinline__ void tile_store(__amdgpu_buffer_rsrc_t rs, uint32_t Ns, uint32_t n,
@@ -403,10 +423,12 @@ __device__ __forceinline__ void tile_macro(__amdgpu_buffer_rsrc_t rin,
     frame_pos<TX, TY, 2>(h, hx, hy);
     typename GWord<P>::T w[9];
     tile_load_g<P, EDGE>(rin, Ns, tile_node(x0 + hx, y0 + hy, g), w);
-    lphi[(hy + 2) * PX + hx + 2] = g_words_phi<P>(w);
+    lphi[(hy + 2) * PX + hx + 2] = moment_phi<P>(w);
   }
   int32_t phi_q = 0;
-  const T ph = row_phi<P>(row, phi_q);
+  T ph;
+  if constexpr (P == P_F16) ph = moment_phi<P>(row.w);
+  else ph = row_phi<P>(row, phi_q);
   lphi[e] = ph;
   __syncthreads();
   T v[3][3], gphx, gphy, lapphi, gmux, gmuy, lapmu;
@@ -475,7 +497,7 @@ __global__ __launch_bounds__(256) void k_phi_out(Pop<P> in, double* __restrict__
   const int y = (int)((uint32_t)n / (uint32_t)g.nx), x = (int)((uint32_t)n - (uint32_t)y * g.nx);
   typename GWord<P>::T w[9];
   tile_load_g<P, true>(rin, (uint32_t)g.Ns, tile_node(x, y, g), w);
-  phi[n] = double(g_words_phi<P>(w));
+  phi[n] = double(moment_phi<P>(w));
 }
 
 // phi of a node's words exactly, in binary64 (summed like pull_phi_exact).
