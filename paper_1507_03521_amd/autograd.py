@@ -62,7 +62,7 @@ class PhaseFieldRun(torch.autograd.Function):
         (phi0,) = ctx.saved_tensors
         lat, snaps, C, K = ctx.lat, ctx.snaps, ctx.C, ctx.K
         lat.adjoint_begin(dphi.detach().to(torch.float64).contiguous())
-        held = _records(lat, min(C, K))
+        held = _records(lat, max(0, min(C, K)))
         records = lat.record_array(held)
         for s in reversed(range(len(snaps))):
             n = min(C, K - s * C)
