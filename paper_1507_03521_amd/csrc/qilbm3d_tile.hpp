@@ -92,7 +92,9 @@ __device__ __forceinline__ typename PrecT<P>::T tphi(const PopView<P, BIG>& v, c
   else return s;
 }
 
-// Tile (tx, ty, tz) of the launch, and whether a wall layer is within reach.
+// Tile (tx, ty, tz) of the launch. A launch of two dimensions (tile_grid) may
+// have workgroups beyond the last tile: theirs starts beyond the lattice
+// (z0 >= nz).
 struct TileAt {
   int x0, y0, z0;
 };
@@ -100,7 +102,7 @@ template <int TX, int TY, int TZ>
 __device__ __forceinline__ TileAt tile_at(const Geom3& g) {
   const int ntx = (g.nx + TX - 1) / TX, nty = (g.ny + TY - 1) / TY;
   // consecutive tiles, which share halo nodes, on one XCD
-  const int b = xcd_tile((int)blockIdx.x, (int)gridDim.x);
+  const int b = xcd_tile((int)(blockIdx.y * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y));
   const int tz = b / (ntx * nty), r = b - tz * (ntx * nty);
   const int ty = r / ntx, tx = r - ty * ntx;
   return {tx * TX, ty * TY, tz * TZ};
@@ -108,6 +110,14 @@ __device__ __forceinline__ TileAt tile_at(const Geom3& g) {
 template <int TX, int TY, int TZ>
 inline int64_t tile_count(const Geom3& g) {
   return (int64_t)((g.nx + TX - 1) / TX) * ((g.ny + TY - 1) / TY) * ((g.nz + TZ - 1) / TZ);
+}
+
+// Grid of n workgroups of t lanes: a launch holds less than 2^32 lanes in a
+// dimension, which a lattice three nodes wide exceeds (13 idle lanes for
+// three; FP32 3 x 5 x 34 million).
+inline dim3 tile_grid(int64_t n, int t) {
+  const int64_t rows = n * t / ((int64_t)1 << 31) + 1;
+  return dim3((unsigned)((n + rows - 1) / rows), (unsigned)rows);
 }
 
 // A tile shape, with the addressing of populations beyond 4 GiB or without.
@@ -290,6 +300,7 @@ __global__ __launch_bounds__(TX * TY * TZ) void k3_tile_f(
   __shared__ T lmu[Reg3<TX, TY, TZ, 1>::A];
   const PopView<P, BIG> v(in), w(out);
   const TileAt o = tile_at<TX, TY, TZ>(g);
+  if (o.z0 >= g.nz) return;
   const int t = threadIdx.x, lx = t % TX, ly = t / TX % TY, lz = t / (TX * TY);
   const int x = o.x0 + lx, y = o.y0 + ly, z = o.z0 + lz;
   const TNode k = tnode<sizeof(T)>(x, y, z, g);
@@ -328,6 +339,7 @@ __global__ __launch_bounds__(TX * TY * TZ) void k3_tile_macro(
   __shared__ T lmu[Reg3<TX, TY, TZ, 1>::A];
   const PopView<P, BIG> v(in);
   const TileAt o = tile_at<TX, TY, TZ>(g);
+  if (o.z0 >= g.nz) return;
   const int t = threadIdx.x, lx = t % TX, ly = t / TX % TY, lz = t / (TX * TY);
   const int x = o.x0 + lx, y = o.y0 + ly, z = o.z0 + lz;
   const TNode k = tnode<sizeof(T)>(x, y, z, g);
@@ -368,6 +380,7 @@ __global__ __launch_bounds__(TX * TY * TZ) void k3_tile_g(
   const Planes<T, false> phf(phi, g.Ns, 1), mf(mu, g.Ns, 1), pf(p, g.Ns, 1);
   const Planes<T, false> jf[3] = {{jx, g.Ns, 1}, {jy, g.Ns, 1}, {jz, g.Ns, 1}};
   const TileAt o = tile_at<TX, TY, TZ>(g);
+  if (o.z0 >= g.nz) return;
   const int t = threadIdx.x, lx = t % TX, ly = t / TX % TY, lz = t / (TX * TY);
   const int x = o.x0 + lx, y = o.y0 + ly, z = o.z0 + lz;
   const bool owns = x < g.nx && y < g.ny && z < g.nz;
