@@ -232,9 +232,9 @@ template <int P>
 lbm_status moments_p(lbm_ctx* c, const MomentOut& mo) {
   using T = typename PrecT<P>::T;
   const Coef<T> k = coef_t<T>(c);
-  if (moments_fit<P>(c->geom))
+  if (moments_tiled<P>(c->geom, mo))
     return st(launch_moments<P>(c->pop[c->cur], mo, k, c->geom, c->stream));
-  hipError_t e = launch_fields<P>(c->pop[c->cur], phi_f(c), mu_f(c), k, c->geom, c->stream);
+  hipError_t e = launch_moment_fields<P>(c->pop[c->cur], phi_f(c), mu_f(c), k, c->geom, c->stream);
   if (e != hipSuccess) return LBM_EDEVICE;
   return st(launch_macro<P>(c->pop[c->cur], phi_f(c), mu_f(c), nullptr, nullptr, mo, k, c->geom,
                             c->stream));

@@ -109,15 +109,26 @@ template <int P>
 hipError_t launch_step2_tile(const void* pin, void* pout, const Coef<typename PrecT<P>::T>& c,
                              const Geom& g, void* rec0, void* rec1, hipStream_t s, bool trt);
 
-// FP64 moments into mo in one pass, where moments_fit (else launch_fields and
-// launch_macro).
+// FP64 moments into mo in one pass, where moments_tiled (else
+// launch_moment_fields and launch_macro). moments_fit: the populations are
+// within reach of these kernels' 32-bit offsets.
 template <int P>
 bool moments_fit(const Geom& g);
+template <int P>
+bool moments_tiled(const Geom& g, const MomentOut& mo);
+// phi of the moments as a field (O: the compute type) or as an output, where
+// moments_fit; and that field and mu's for launch_macro.
+template <int P, typename O>
+hipError_t launch_phi(const void* pop, O* phi, const Geom& g, hipStream_t s);
+template <int P>
+hipError_t launch_moment_fields(const void* pop, void* phi, void* mu,
+                                const Coef<typename PrecT<P>::T>& c, const Geom& g, hipStream_t s);
 template <int P>
 hipError_t launch_moments(const void* pop, const MomentOut& mo,
                           const Coef<typename PrecT<P>::T>& c, const Geom& g, hipStream_t s);
 // Partials of the totals: mass_blocks(g) rows of four in launch_mass.
 constexpr int MASS_BLOCKS = 2048;
+bool mass_tiled(const Geom& g);
 int mass_blocks(const Geom& g);
 template <int P>
 hipError_t launch_mass_tiles(const void* pop, double* part, const Coef<typename PrecT<P>::T>& c,

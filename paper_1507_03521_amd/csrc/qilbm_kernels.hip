@@ -1460,6 +1460,18 @@ hipError_t launch_fields(const void* pop, void* phi, void* mu,
 }
 
 template <int P>
+hipError_t launch_moment_fields(const void* pop, void* phi, void* mu,
+                                const Coef<typename PrecT<P>::T>& c, const Geom& g,
+                                hipStream_t s) {
+  using T = typename PrecT<P>::T;
+  if (!moments_fit<P>(g)) return launch_fields<P>(pop, phi, mu, c, g, s);
+  const hipError_t e = launch_phi<P>(pop, (T*)phi, g, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_mu<T>, dim3(nblk(g.N, 256)), dim3(256), 0, s, (const T*)phi, (T*)mu, c, g);
+  return hipGetLastError();
+}
+
+template <int P>
 hipError_t launch_macro(const void* pop, const void* phi, const void* mu, void* p, void* sj,
                         const MomentOut& mo, const Coef<typename PrecT<P>::T>& c, const Geom& g,
                         hipStream_t s) {
@@ -1643,11 +1655,11 @@ hipError_t launch_mass(const void* pop, void* phi, void* mu, double* part, int n
                        const Geom& g, hipStream_t s) {
   using T = typename PrecT<P>::T;
   hipError_t e;
-  if (moments_fit<P>(g)) {
+  if (moments_fit<P>(g) && mass_tiled(g)) {
     e = launch_mass_tiles<P>(pop, part, c, c64, g, s);
     if (e != hipSuccess) return e;
   } else {
-    e = launch_fields<P>(pop, phi, mu, c, g, s);
+    e = launch_moment_fields<P>(pop, phi, mu, c, g, s);
     if (e != hipSuccess) return e;
     Pop<P> i{(char*)pop, g.Ns};
     hipLaunchKernelGGL(k_mass_partial<P>, dim3(nred), dim3(256), 0, s, i, (const T*)phi,
@@ -1672,6 +1684,9 @@ hipError_t launch_sum_partials(const double* part, int nb, int width, double* ou
                                              hipStream_t);                                       \
   template hipError_t launch_fields<P>(const void*, void*, void*,                                \
                                        const Coef<PrecT<P>::T>&, const Geom&, hipStream_t);      \
+  template hipError_t launch_moment_fields<P>(const void*, void*, void*,                         \
+                                              const Coef<PrecT<P>::T>&, const Geom&,             \
+                                              hipStream_t);                                      \
   template hipError_t launch_macro<P>(const void*, const void*, const void*, void*, void*,     \
                                       const MomentOut&, const Coef<PrecT<P>::T>&, const Geom&,   \
                                       hipStream_t);                                              \

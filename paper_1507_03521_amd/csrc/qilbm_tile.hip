@@ -487,9 +487,10 @@ __global__ __launch_bounds__(TX * TY) void k_tile_moments(Pop<P> in, MomentOut m
   if (mo.mu) mo.mu[n] = double(m.mu);
 }
 
-// phi alone needs no neighbours.
-template <int P>
-__global__ __launch_bounds__(256) void k_phi_out(Pop<P> in, double* __restrict__ phi, Geom g,
+// phi alone needs no neighbours: as an output (O double) or as the field that
+// k_mu and k_macro read (O the compute type).
+template <int P, typename O>
+__global__ __launch_bounds__(256) void k_phi_out(Pop<P> in, O* __restrict__ phi, Geom g,
                                                  uint32_t bytes) {
   const __amdgpu_buffer_rsrc_t rin = __builtin_amdgcn_make_buffer_rsrc(in.base, 0, (int)bytes, BUF_WORD3);
   const int64_t n = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
@@ -497,7 +498,7 @@ __global__ __launch_bounds__(256) void k_phi_out(Pop<P> in, double* __restrict__
   const int y = (int)((uint32_t)n / (uint32_t)g.nx), x = (int)((uint32_t)n - (uint32_t)y * g.nx);
   typename GWord<P>::T w[9];
   tile_load_g<P, true>(rin, (uint32_t)g.Ns, tile_node(x, y, g), w);
-  phi[n] = double(moment_phi<P>(w));
+  phi[n] = O(moment_phi<P>(w));
 }
 
 // phi of a node's words exactly, in binary64 (summed like pull_phi_exact).
@@ -661,6 +662,35 @@ bool moments_fit(const Geom& g) {
   return pop_bytes(P, g.Ns) <= (int64_t)UINT32_MAX;
 }
 
+// Tile of the moments: 64 wide ones of little halo where they are two rounds
+// of workgroups and more (2048 x 8192, 64 x 16, 64 x 8, 32 x 8, 16 x 8: fp32
+// 333, 358, 426, 515 us; fp64 596, 569, 631, 711), else small ones.
+enum MomentShape { M16x8, M64x16, M64x8 };
+template <int P>
+MomentShape moment_shape(const Geom& g) {
+  if (tiles(g, 64, 8) < 2 * CUS) return M16x8;
+  return P == P_F32 ? M64x16 : M64x8;
+}
+
+// On a lattice of few columns most lanes of a tile have no node, and the
+// kernels of a node per thread (launch_moment_fields, launch_macro) are the
+// faster ones (us, tiles against them, 1 M nodes: fp64 nx = 3 247 and 41, 10 76
+// and 41, 16 50 and 40, 20 41 and 41, 24 36 and 41; fp32 16 36 and 35; 200 k nodes:
+// fp64 3 52 and 18, 10 18.5 and 17.5, 12 17 and 18). Up to a million lanes their
+// three launches take longer than the idle lanes.
+template <int P>
+bool moments_tiled(const Geom& g, const MomentOut& mo) {
+  if (!moments_fit<P>(g)) return false;
+  if (mo.phi && !mo.rho && !mo.ux && !mo.uy && !mo.p && !mo.mu) return true;
+  int64_t lanes;
+  switch (moment_shape<P>(g)) {
+    case M16x8: lanes = tiles(g, 16, 8) * (int64_t)128; break;
+    case M64x16: lanes = tiles(g, 64, 16) * (int64_t)1024; break;
+    default: lanes = tiles(g, 64, 8) * (int64_t)512; break;
+  }
+  return lanes <= 1200000 || 2 * lanes <= 7 * g.N;
+}
+
 template <int P, int TX, int TY>
 void launch_moments_tile(const Pop<P>& in, const MomentOut& mo,
                          const Coef<typename PrecT<P>::T>& c, const Geom& g, hipStream_t s) {
@@ -668,28 +698,39 @@ void launch_moments_tile(const Pop<P>& in, const MomentOut& mo,
                      mo, c, g, (g.nx + TX - 1) / TX, (uint32_t)pop_bytes(P, g.Ns));
 }
 
+template <int P, typename O>
+hipError_t launch_phi(const void* pop, O* phi, const Geom& g, hipStream_t s) {
+  hipLaunchKernelGGL((k_phi_out<P, O>), dim3((unsigned)((g.N + 255) / 256)), dim3(256), 0, s,
+                     Pop<P>{(char*)pop, g.Ns}, phi, g, (uint32_t)pop_bytes(P, g.Ns));
+  return hipGetLastError();
+}
+
 template <int P>
 hipError_t launch_moments(const void* pop, const MomentOut& mo,
                           const Coef<typename PrecT<P>::T>& c, const Geom& g, hipStream_t s) {
   const Pop<P> in{(char*)pop, g.Ns};
-  if (mo.phi && !mo.rho && !mo.ux && !mo.uy && !mo.p && !mo.mu) {
-    hipLaunchKernelGGL(k_phi_out<P>, dim3((unsigned)((g.N + 255) / 256)), dim3(256), 0, s, in,
-                       mo.phi, g, (uint32_t)pop_bytes(P, g.Ns));
-    return hipGetLastError();
+  if (mo.phi && !mo.rho && !mo.ux && !mo.uy && !mo.p && !mo.mu)
+    return launch_phi<P>(pop, mo.phi, g, s);
+  switch (moment_shape<P>(g)) {
+    case M16x8: launch_moments_tile<P, 16, 8>(in, mo, c, g, s); break;
+    case M64x16: launch_moments_tile<P, 64, 16>(in, mo, c, g, s); break;
+    default: launch_moments_tile<P, 64, 8>(in, mo, c, g, s); break;
   }
-  // 64 wide tiles of little halo where they are two rounds of workgroups and
-  // more (2048 x 8192, 64 x 16, 64 x 8, 32 x 8, 16 x 8: fp32 333, 358, 426, 515
-  // us; fp64 596, 569, 631, 711), else small ones
-  if (tiles(g, 64, 8) < 2 * CUS) launch_moments_tile<P, 16, 8>(in, mo, c, g, s);
-  else if (P == P_F32) launch_moments_tile<P, 64, 16>(in, mo, c, g, s);
-  else launch_moments_tile<P, 64, 8>(in, mo, c, g, s);
   return hipGetLastError();
+}
+
+// Totals likewise, from 600 thousand lanes on (us, tiles against a node per
+// thread, fp64: 1 M nodes, nx = 3 158 and 70, 8 81 and 70, 10 71 and 70, 12 65
+// and 70; 200 k, 3 58 and 40, 10 41 and 40; 40 k, 3 35 and 37).
+bool mass_tiled(const Geom& g) {
+  const int64_t lanes = tiles(g, MASS_TX, MASS_TY) * (int64_t)(MASS_TX * MASS_TY);
+  return lanes <= 600000 || lanes <= 3 * g.N;
 }
 
 // Workgroups of the totals kernel, one partial each.
 int mass_blocks(const Geom& g) {
-  const int n = tiles(g, MASS_TX, MASS_TY);
-  return n < MASS_BLOCKS ? n : MASS_BLOCKS;
+  const int64_t n = mass_tiled(g) ? tiles(g, MASS_TX, MASS_TY) : (g.N + 255) / 256;
+  return n < MASS_BLOCKS ? (int)n : MASS_BLOCKS;
 }
 
 template <int P>
@@ -705,6 +746,9 @@ hipError_t launch_mass_tiles(const void* pop, double* part, const Coef<typename 
 #define QILBM_INSTANTIATE(P)                                                                     \
   template bool tile_fits<P>(const Geom&);                                                       \
   template bool moments_fit<P>(const Geom&);                                                     \
+  template bool moments_tiled<P>(const Geom&, const MomentOut&);                                 \
+  template hipError_t launch_phi<P, PrecT<P>::T>(const void*, PrecT<P>::T*, const Geom&,         \
+                                                 hipStream_t);                                   \
   template hipError_t launch_moments<P>(const void*, const MomentOut&,                           \
                                         const Coef<PrecT<P>::T>&, const Geom&, hipStream_t);     \
   template hipError_t launch_mass_tiles<P>(const void*, double*, const Coef<PrecT<P>::T>&,       \
