@@ -234,7 +234,7 @@ template <int P, int IX, int IY, int PX, int PY, int NT, int NM_, bool FROM_MID,
 __device__ __forceinline__ void tile_phase(__amdgpu_buffer_rsrc_t rin, __amdgpu_buffer_rsrc_t rout,
                                            const Coef<typename PrecT<P>::T>& c, const Geom& g,
                                            int bx, int by, int ox, int TXr, int TYr,
-                                           typename PrecT<P>::T* rec,
+                                           typename PrecT<P>::T* rec, bool rec_stream,
                                            TileRings<typename PrecT<P>::T, PX, PY>& L, MID& M) {
   using T = typename PrecT<P>::T;
   constexpr int NI = IX * IY, NR = frame_count<IX, IY, 1>(), NP = NI + NR;
@@ -328,12 +328,18 @@ __device__ __forceinline__ void tile_phase(__amdgpu_buffer_rsrc_t rin, __amdgpu_
     macro_node(ph, mu, gphx, gphy, gmux, gmuy, lapmu, S, jx, jy, c, m);
     L.p[e] = m.p;
     if (rec && owns) {
-      rec[n] = ph;
-      rec[g.Ns + n] = mu;
-      rec[2 * g.Ns + n] = m.p;
-      rec[3 * g.Ns + n] = S;
-      rec[4 * g.Ns + n] = jx;
-      rec[5 * g.Ns + n] = jy;
+      const T v[6] = {ph, mu, m.p, S, jx, jy};
+      if (rec_stream) {
+        const uint32_t pb = Ns * (uint32_t)sizeof(T);
+        const __amdgpu_buffer_rsrc_t rr =
+            __builtin_amdgcn_make_buffer_rsrc(rec, 0, (int)(6 * pb), BUF_WORD3);
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+          buf_st<T, ST_STREAM>(v[q], rr, (uint32_t)n * (uint32_t)sizeof(T), q * pb);
+      } else {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) rec[q * g.Ns + n] = v[q];
+      }
     }
   }
   __syncthreads();
@@ -354,15 +360,15 @@ __device__ __forceinline__ void tile_phase(__amdgpu_buffer_rsrc_t rin, __amdgpu_
 // K steps of the lattice; tile (i, j) starts at node (i TX, j TY). Beyond the
 // lattice's last column a tile goes on with the wrapped columns (computed,
 // not stored); so it does beyond the last row when periodic.
-// rec0, rec1: records of the states the steps start from, or null. Whether
-// they are written is a uniform branch and not a variant of the kernel: the
+// rec0, rec1: records of the states the steps start from, or null, stored as a
+// stream with rec_stream. Whether and how they are written is a uniform branch and not a variant of the kernel: the
 // compiler contracts multiply-adds per kernel, and a recording replay must
 // reproduce the plain steps bit for bit.
 template <int P, int K, int TX, int TY, int NT, bool TRT, int POL>
 __global__ __launch_bounds__(NT) void k_tile(Pop<P> in, Pop<P> out, Coef<typename PrecT<P>::T> c,
                                              Geom g, int ntx, uint32_t bytes,
                                              typename PrecT<P>::T* rec0,
-                                             typename PrecT<P>::T* rec1) {
+                                             typename PrecT<P>::T* rec1, bool rec_stream) {
   using T = typename PrecT<P>::T;
   static_assert(K == 1 || K == 2, "steps per launch");
   constexpr int O = 4 * (K - 1);                 // first step's interior beyond the tile
@@ -381,24 +387,24 @@ __global__ __launch_bounds__(NT) void k_tile(Pop<P> in, Pop<P> out, Coef<typenam
   if constexpr (K == 2) {
     if (edge) {
       tile_phase<P, TX + 8, TY + 8, PX, PY, NT, NM_, false, true, true, TRT, POL>(
-          rin, rout, c, g, x0 - 4, y0 - 4, 4, TX, TY, rec0, L, M);
+          rin, rout, c, g, x0 - 4, y0 - 4, 4, TX, TY, rec0, rec_stream, L, M);
       __syncthreads();
       tile_phase<P, TX, TY, PX, PY, NT, NM_, true, false, true, TRT, POL>(
-          rin, rout, c, g, x0, y0, 0, TX, TY, rec1, L, M);
+          rin, rout, c, g, x0, y0, 0, TX, TY, rec1, rec_stream, L, M);
     } else {
       tile_phase<P, TX + 8, TY + 8, PX, PY, NT, NM_, false, true, false, TRT, POL>(
-          rin, rout, c, g, x0 - 4, y0 - 4, 4, TX, TY, rec0, L, M);
+          rin, rout, c, g, x0 - 4, y0 - 4, 4, TX, TY, rec0, rec_stream, L, M);
       __syncthreads();
       tile_phase<P, TX, TY, PX, PY, NT, NM_, true, false, false, TRT, POL>(
-          rin, rout, c, g, x0, y0, 0, TX, TY, rec1, L, M);
+          rin, rout, c, g, x0, y0, 0, TX, TY, rec1, rec_stream, L, M);
     }
   } else {
     if (edge)
       tile_phase<P, TX, TY, PX, PY, NT, NM_, false, false, true, TRT, POL>(
-          rin, rout, c, g, x0, y0, 0, TX, TY, rec0, L, M);
+          rin, rout, c, g, x0, y0, 0, TX, TY, rec0, rec_stream, L, M);
     else
       tile_phase<P, TX, TY, PX, PY, NT, NM_, false, false, false, TRT, POL>(
-          rin, rout, c, g, x0, y0, 0, TX, TY, rec0, L, M);
+          rin, rout, c, g, x0, y0, 0, TX, TY, rec0, rec_stream, L, M);
   }
 }
 
@@ -554,6 +560,18 @@ __global__ __launch_bounds__(256) void k_tile_mass(Pop<P> in, double* __restrict
   block_sum4(a, part + 4 * blockIdx.x);
 }
 
+// Whether records are stored as a stream: where they and the two population
+// buffers exceed what the Infinity Cache keeps, they would push the populations
+// out of it, and a record is next read after a whole segment (us per recorded
+// step, plain and as a stream: fp32 1143 x 1487 86 and 50, 1000 x 1300 44 and 39;
+// fp16 1640 x 2134 132 and 81; fp64 1000 x 780 65 and 45). Below, the adjoint still
+// finds them there (recorded and adjoint step, fp32 554 x 722 46 and 48).
+template <int P>
+bool records_stream(const Geom& g) {
+  return 2 * pop_bytes(P, g.Ns) + 6 * g.Ns * (int64_t)sizeof(typename PrecT<P>::T) >
+         (int64_t)190 << 20;
+}
+
 // ------------------------------------------------------------- dispatch
 // Measured on MI355X (us per step, row-sweeping kernel -> tiles; fp64 / fp32
 // at two steps per pass, fp16 storage at one):
@@ -578,7 +596,7 @@ void launch_tile(const void* pin, void* pout, const Coef<typename PrecT<P>::T>& 
   const Pop<P> i{(char*)pin, g.Ns}, o{(char*)pout, g.Ns};
   hipLaunchKernelGGL((k_tile<P, K, TX, TY, NT, TRT, POL>), dim3(tiles(g, TX, TY)), dim3(NT), 0, s,
                      i, o, c, g, (g.nx + TX - 1) / TX, (uint32_t)pop_bytes(P, g.Ns), (T*)rec0,
-                     (T*)rec1);
+                     (T*)rec1, records_stream<P>(g));
 }
 
 // Whether the one-step kernel writes its results through. Lines that a kernel leaves
