@@ -1057,6 +1057,39 @@ AdjLayout adj_layout(const lbm_params* p) {
   return L;
 }
 
+// Strips of at most 248 columns; one round of workgroups (every segment end
+// recomputes 4 rows).
+template <typename T>
+AdjShape adj_shape(AdjointState& a, const Geom& g) {
+  if (a.resident <= 0) {
+    int dev = 0, cus = 0, per_cu = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_adj_fused<T, false>, ANT, 0) ==
+            hipSuccess)
+      a.resident = cus * (per_cu > 0 ? per_cu : 1);
+    if (a.resident <= 0) a.resident = 256;
+  }
+  AdjShape sh;
+  const int fw = ANT - 2 * AH;
+  sh.nstrips = (g.nx + fw - 1) / fw;
+  sh.width = (g.nx + sh.nstrips - 1) / sh.nstrips;
+  sh.nseg = a.resident / sh.nstrips;
+  if (sh.nseg < 1) sh.nseg = 1;
+  sh.seg = (g.ny + sh.nseg - 1) / sh.nseg;
+  if (sh.seg < 16) sh.seg = 16;
+  if (sh.seg > g.ny) sh.seg = g.ny;
+  sh.nseg = (g.ny + sh.seg - 1) / sh.seg;
+  sh.resident = a.resident;
+  return sh;
+}
+
+// Tiles of the tiled step, 0 where the row sweep runs.
+template <typename T>
+int adj_tiles(AdjointState& a, const Geom& g) {
+  return adj_tile_fits<T>(g, adj_shape<T>(a, g)) ? adj_tile_count<T>(g) : 0;
+}
+
 // One adjoint step from the record of forward step t.
 template <typename T>
 lbm_status adj_core(const CtxView& v, const T* rec) {
@@ -1076,34 +1109,16 @@ lbm_status adj_core(const CtxView& v, const T* rec) {
     if (launch_adj_tile<T>(rec, hin, hout, a.tpart, k, g, v.stream) != hipSuccess)
       return LBM_EDEVICE;
   } else {
-    // strips of at most 248 columns; one round of workgroups (every segment
-    // end recomputes 4 rows); at most nred workgroups, one partial slot each
-    const int fw = ANT - 2 * AH;
-    const int nstrips = (g.nx + fw - 1) / fw;
-    const int width = (g.nx + nstrips - 1) / nstrips;
-    if (a.resident <= 0) {
-      int dev = 0, cus = 0, per_cu = 0;
-      if (hipGetDevice(&dev) == hipSuccess &&
-          hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-          hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_adj_fused<T, false>, ANT, 0) ==
-              hipSuccess)
-        a.resident = cus * (per_cu > 0 ? per_cu : 1);
-      if (a.resident <= 0) a.resident = 256;
-    }
-    int nseg = a.resident / nstrips;
-    if (nseg < 1) nseg = 1;
-    int seg = (g.ny + nseg - 1) / nseg;
-    if (seg < 16) seg = 16;
-    if (seg > g.ny) seg = g.ny;
-    nseg = (g.ny + seg - 1) / seg;
-    const int ntiles = nstrips * nseg;
+    // at most nred workgroups, one partial slot each
+    const AdjShape sh = adj_shape<T>(a, g);
+    const int ntiles = sh.nstrips * sh.nseg;
     const int nblk = ntiles < a.nred ? ntiles : a.nred;
     if (18 * g.Ns * (int64_t)sizeof(T) > (int64_t)UINT32_MAX)
       hipLaunchKernelGGL((k_adj_fused<T, true>), dim3(nblk), dim3(ANT), 0, v.stream, rec, hin,
-                         hout, a.part, k, g, width, nstrips, seg, ntiles);
+                         hout, a.part, k, g, sh.width, sh.nstrips, sh.seg, ntiles);
     else
       hipLaunchKernelGGL((k_adj_fused<T, false>), dim3(nblk), dim3(ANT), 0, v.stream, rec, hin,
-                         hout, a.part, k, g, width, nstrips, seg, ntiles);
+                         hout, a.part, k, g, sh.width, sh.nstrips, sh.seg, ntiles);
   }
   if (hipGetLastError() != hipSuccess) return LBM_EDEVICE;
   a.cur ^= 1;
@@ -1208,12 +1223,9 @@ lbm_status lbm_adjoint_begin(lbm_ctx* ctx, void* ws, size_t bytes, const double*
   a.nred = L.nred;
   a.tpart = (double*)a.afld;
   a.ntiles = 0;
-  if (!(v.prm->flags & LBM_FLAG_UNFUSED)) {
-    if (v.prm->precision == LBM_FP64)
-      a.ntiles = adj_tile_fits<double>(v.geom) ? adj_tile_count<double>(v.geom) : 0;
-    else
-      a.ntiles = adj_tile_fits<float>(v.geom) ? adj_tile_count<float>(v.geom) : 0;
-  }
+  if (!(v.prm->flags & LBM_FLAG_UNFUSED))
+    a.ntiles = v.prm->precision == LBM_FP64 ? adj_tiles<double>(a, v.geom)
+                                            : adj_tiles<float>(a, v.geom);
   a.active = true;
   return lbm_adjoint_seed(ctx, dL_dphi);
 }

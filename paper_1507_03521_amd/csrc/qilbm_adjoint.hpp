@@ -52,11 +52,17 @@ struct CtxView {
 
 CtxView ctx_view(lbm_ctx* c);
 
+// Launch shape of the row-sweeping adjoint: strips of width columns, segments of
+// seg rows, and the workgroups that are resident at once.
+struct AdjShape {
+  int nstrips, width, nseg, seg, resident;
+};
+
 // Tiled adjoint step (qilbm_adjoint_tile.hip) of lattices small enough for it
 // (adj_tile_fits): replaces the cotangents hin by hout and adds each tile's
 // four parameter sums to its slot of part (adj_tile_count tiles).
 template <typename T>
-bool adj_tile_fits(const Geom& g);
+bool adj_tile_fits(const Geom& g, const AdjShape& sh);
 template <typename T>
 int adj_tile_count(const Geom& g);
 template <typename T>

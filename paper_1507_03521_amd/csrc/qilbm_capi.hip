@@ -176,10 +176,10 @@ lbm_status step_p(lbm_ctx* c, int64_t n, void* const* recs, const char* src = nu
   };
   // small lattices run as tiles, unless the caller has set the rows per
   // segment of the row-sweeping kernel that would run otherwise
-  const bool small = !unfused && tile_fits<P>(c->geom);
-  const bool tile1 = small && c->seg_rows == 0;
+  const bool tile1 = !unfused && c->seg_rows == 0 && tile_fits<P>(c->geom, 1);
   if constexpr (P != P_F16) {
-    const bool tile2 = small && c->pass_steps == 2 && c->pass_seg_rows == 0;
+    const bool tile2 = !unfused && c->pass_steps == 2 && c->pass_seg_rows == 0 &&
+                       tile_fits<P>(c->geom, 2);
     if (tile2 && tile_steps<P>(c->geom) == 2) {
       while (n - done >= 2) {
         if (launch_step2_tile<P>(in(), out(2), k, c->geom, recs ? recs[done] : nullptr,

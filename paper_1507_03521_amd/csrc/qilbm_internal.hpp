@@ -96,10 +96,10 @@ hipError_t launch_step2_fused(const void* pin, void* pout, const Coef<typename P
                               const Geom& g, const FusedShape& sh, void* rec0, void* rec1,
                               hipStream_t s, bool trt = false);
 // Tiled kernels (qilbm_tile.hip) for lattices small enough for them
-// (tile_fits): one step per launch, or two (P_F64 and P_F32) where
-// tile_steps is 2. Records and trt as for the fused kernels.
+// (tile_fits, for passes of one step or two): one step per launch, or two (P_F64
+// and P_F32) where tile_steps is 2. Records and trt as for the fused kernels.
 template <int P>
-bool tile_fits(const Geom& g);
+bool tile_fits(const Geom& g, int steps);
 template <int P>
 int tile_steps(const Geom& g);
 template <int P>

@@ -628,17 +628,47 @@ hipError_t launch_tile_variant(const void* pin, void* pout, const Coef<typename 
 
 }  // namespace
 
+// Rows of more than 2048 columns (FP32 4 MB of populations in eight rows): the
+// halo rows of a tile have left its XCD's L2 when the tiles below need them,
+// and a lattice of few rows gives the sweep short segments, so it has the
+// shorter time already at smaller sizes. The sweep takes (rows per segment +
+// warm-up) for each round of its workgroups, the tiles a time by the lane,
+// idle ones included; us per step, sweep and tiles: fp32 4095 x 341 44.6 and 45.1, x
+// 424 45 and 55; 24 390 x 41 43 and 36, 31 707 x 41 43 and 46; 50 000 x 12 25 and 22,
+// 83 333 x 12 29 and 35; 22 222 x 9 20 and 12, 66 666 x 9 24 and 26; fp16 4095 x 610
+// 59 and 55; 83 333 x 12 36 and 30, 133 333 x 12 43 and 45; 200 000 x 3 20 and 30;
+// fp64 40 000 x 5 21 and 18, 120 000 x 5 42 and 47.
+template <int P>
+bool tiles_beat_rows(const Geom& g) {
+  if (g.nx <= 2048) return true;
+  if constexpr (P == P_F16) {
+    const FusedShape sh = fused_shape<P>(g, 0, 0);
+    const int64_t wgs = (int64_t)sh.nstrips * sh.nseg;
+    return tiles(g, 32, 8) * (int64_t)256 <= 82000 * (sh.seg_rows + 2) * (860 + wgs) / 860;
+  } else {
+    constexpr int resident = P == P_F64 ? CUS : 2 * CUS;
+    const FusedShape sh = fused2_shape<P>(g, 0, resident);
+    const int64_t rounds = ((int64_t)sh.nstrips * sh.nseg + resident - 1) / resident;
+    if constexpr (P == P_F64)
+      return tiles(g, 32, 4) * (int64_t)128 <= 42000 * rounds * (sh.seg_rows + 4);
+    return 2 * pop_bytes(P, g.Ns) <= (int64_t)205 << 20 &&
+           tiles(g, 32, 8) * (int64_t)256 <= 70000 * rounds * (sh.seg_rows + 5);
+  }
+}
+
 // Tiles while both population buffers together stay within the 256 MB
 // Infinity Cache: a tile reads its halo again from L2 and beyond, which is
 // cheap only there. Past it the row sweep, which moves the state once per two
 // steps, is faster (us per step, row sweep against tiles): fp64 at 884 k nodes
 // (254 MB) 40.1 and 44.0, at 810 k 39.8 and 40.4, at 750 k 39.6 and 38.2, at 640 k
-// (184 MB) 39.4 and 33.1; fp32 at 2.0 M nodes (289 MB) 53 and 69, at 1.2 M (174 MB)
-// 45 and 33; fp16 storage at 4.2 M nodes (319 MB) 103 and 116, at 2.0 M (152 MB)
-// 58 and 44. The limit also keeps every byte offset in a buffer below 2^31.
+// (184 MB) 39.4 and 33.1; fp32 pairs at 1.85 M nodes (266 MB) 44.5 and 46.4, at 1.6 M
+// 44.1 and 41, single steps at 1.74 M 50 and 45; fp16 storage at 3.5 M nodes (266
+// MB) 69 and 73, at 2.8 M 58 and 58, at 2.0 M 58 and 44. The limit also keeps
+// every byte offset in a buffer below 2^31. steps: of a pass.
 template <int P>
-bool tile_fits(const Geom& g) {
-  return 2 * pop_bytes(P, g.Ns) <= (int64_t)(P == P_F64 ? 220 : 256) << 20;
+bool tile_fits(const Geom& g, int steps) {
+  const int mib = P == P_F64 ? 220 : (P == P_F32 && steps == 1 ? 256 : 224);
+  return 2 * pop_bytes(P, g.Ns) <= (int64_t)mib << 20 && tiles_beat_rows<P>(g);
 }
 
 template <int P>
@@ -762,7 +792,7 @@ hipError_t launch_mass_tiles(const void* pop, double* part, const Coef<typename 
 }
 
 #define QILBM_INSTANTIATE(P)                                                                     \
-  template bool tile_fits<P>(const Geom&);                                                       \
+  template bool tile_fits<P>(const Geom&, int);                                                  \
   template bool moments_fit<P>(const Geom&);                                                     \
   template bool moments_tiled<P>(const Geom&, const MomentOut&);                                 \
   template hipError_t launch_phi<P, PrecT<P>::T>(const void*, PrecT<P>::T*, const Geom&,         \
