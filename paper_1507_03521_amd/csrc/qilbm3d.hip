@@ -1496,7 +1496,7 @@ void launch_tile_phi(lbm3_ctx* c, TL) {
   const Geom3& g = c->geom;
   const Pop3<P> in{c->pop[c->cur], g.Ns};
   hipLaunchKernelGGL((k3_tile_phi<P, TL::big, TL::x, TL::y, TL::z>),
-                     tile_grid(TL::count(g), TL::n), dim3(TL::n), 0, c->stream, in,
+                     TL::grid(g), dim3(TL::n), 0, c->stream, in,
                      Fields3<typename PrecT<P>::T>(c).phi, g);
 }
 
@@ -1532,7 +1532,7 @@ hipError_t step_tiles_pol(lbm3_ctx* c) {
   const Coef3<T> k = coef3<T>(c);
   return with_tile<P>(g, [&](auto tl) {
     using TL = decltype(tl);
-    const dim3 grid = tile_grid(TL::count(g), TL::n), block(TL::n);
+    const dim3 grid = TL::grid(g), block(TL::n);
     launch_tile_phi<P>(c, tl);
     if (c->prm.trt_magic > 0.0)
       hipLaunchKernelGGL((k3_tile_f<P, TL::big, true, POL, TL::x, TL::y, TL::z>), grid, block, 0,
@@ -1702,7 +1702,7 @@ lbm_status moments_p(lbm3_ctx* c, const MomentOut3& mo) {
     using TL = decltype(tl);
     launch_tile_phi<P>(c, tl);
     hipLaunchKernelGGL((k3_tile_macro<P, TL::big, TL::x, TL::y, TL::z>),
-                       tile_grid(TL::count(g), TL::n), dim3(TL::n), 0, c->stream, in,
+                       TL::grid(g), dim3(TL::n), 0, c->stream, in,
                        (const T*)Fields3<T>(c).phi, mo, coef3<T>(c), g);
   }));
 }

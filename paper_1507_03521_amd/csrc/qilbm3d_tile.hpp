@@ -92,17 +92,24 @@ __device__ __forceinline__ typename PrecT<P>::T tphi(const PopView<P, BIG>& v, c
   else return s;
 }
 
-// Tile (tx, ty, tz) of the launch. A launch of two dimensions (tile_grid) may
-// have workgroups beyond the last tile: theirs starts beyond the lattice
-// (z0 >= nz).
+// Tile (tx, ty, tz) of the launch. The launch of a BIG lattice has two dimensions
+// (tile_grid) and may have workgroups beyond the last tile: theirs starts beyond
+// the lattice (z0 >= nz).
 struct TileAt {
   int x0, y0, z0;
 };
-template <int TX, int TY, int TZ>
+template <bool BIG, int TX, int TY, int TZ>
 __device__ __forceinline__ TileAt tile_at(const Geom3& g) {
   const int ntx = (g.nx + TX - 1) / TX, nty = (g.ny + TY - 1) / TY;
   // consecutive tiles, which share halo nodes, on one XCD
-  const int b = xcd_tile((int)(blockIdx.y * gridDim.x + blockIdx.x), (int)(gridDim.x * gridDim.y));
+  int b, nb = (int)gridDim.x;
+  if constexpr (BIG) {
+    b = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+    nb *= (int)gridDim.y;
+  } else {
+    b = (int)blockIdx.x;
+  }
+  b = xcd_tile(b, nb);
   const int tz = b / (ntx * nty), r = b - tz * (ntx * nty);
   const int ty = r / ntx, tx = r - ty * ntx;
   return {tx * TX, ty * TY, tz * TZ};
@@ -113,7 +120,7 @@ inline int64_t tile_count(const Geom3& g) {
 }
 
 // Grid of n workgroups of t lanes: a launch holds less than 2^32 lanes in a
-// dimension, which a lattice three nodes wide exceeds (13 idle lanes for
+// dimension, which a BIG lattice three nodes wide exceeds (13 idle lanes for
 // three; FP32 3 x 5 x 34 million).
 inline dim3 tile_grid(int64_t n, int t) {
   const int64_t rows = n * t / ((int64_t)1 << 31) + 1;
@@ -125,7 +132,10 @@ template <bool BIG, int TX, int TY, int TZ>
 struct Tile3 {
   static constexpr bool big = BIG;
   static constexpr int x = TX, y = TY, z = TZ, n = TX * TY * TZ;
-  static int64_t count(const Geom3& g) { return tile_count<TX, TY, TZ>(g); }
+  static dim3 grid(const Geom3& g) {
+    const int64_t c = tile_count<TX, TY, TZ>(g);
+    return BIG ? tile_grid(c, n) : dim3((unsigned)c);
+  }
 };
 
 // LDS region: the tile and H nodes around it.
@@ -234,7 +244,7 @@ __global__ __launch_bounds__(TX * TY * TZ) void k3_tile_phi(Pop3<P> in,
   constexpr int WS = sizeof(T);
   const PopView<P, BIG> v(in);
   const Planes<T, false> out(phi, g.Ns, 1);
-  const TileAt o = tile_at<TX, TY, TZ>(g);
+  const TileAt o = tile_at<BIG, TX, TY, TZ>(g);
   const int t = threadIdx.x, lx = t % TX, ly = t / TX % TY, lz = t / (TX * TY);
   const int x = o.x0 + lx, y = o.y0 + ly, z = o.z0 + lz;
   if (x >= g.nx || y >= g.ny || z >= g.nz) return;
@@ -299,8 +309,8 @@ __global__ __launch_bounds__(TX * TY * TZ) void k3_tile_f(
   __shared__ T lphi[Reg3<TX, TY, TZ, 2>::A];
   __shared__ T lmu[Reg3<TX, TY, TZ, 1>::A];
   const PopView<P, BIG> v(in), w(out);
-  const TileAt o = tile_at<TX, TY, TZ>(g);
-  if (o.z0 >= g.nz) return;
+  const TileAt o = tile_at<BIG, TX, TY, TZ>(g);
+  if (BIG && o.z0 >= g.nz) return;
   const int t = threadIdx.x, lx = t % TX, ly = t / TX % TY, lz = t / (TX * TY);
   const int x = o.x0 + lx, y = o.y0 + ly, z = o.z0 + lz;
   const TNode k = tnode<sizeof(T)>(x, y, z, g);
@@ -338,8 +348,8 @@ __global__ __launch_bounds__(TX * TY * TZ) void k3_tile_macro(
   __shared__ T lphi[Reg3<TX, TY, TZ, 2>::A];
   __shared__ T lmu[Reg3<TX, TY, TZ, 1>::A];
   const PopView<P, BIG> v(in);
-  const TileAt o = tile_at<TX, TY, TZ>(g);
-  if (o.z0 >= g.nz) return;
+  const TileAt o = tile_at<BIG, TX, TY, TZ>(g);
+  if (BIG && o.z0 >= g.nz) return;
   const int t = threadIdx.x, lx = t % TX, ly = t / TX % TY, lz = t / (TX * TY);
   const int x = o.x0 + lx, y = o.y0 + ly, z = o.z0 + lz;
   const TNode k = tnode<sizeof(T)>(x, y, z, g);
@@ -379,8 +389,8 @@ __global__ __launch_bounds__(TX * TY * TZ) void k3_tile_g(
   const PopView<P, BIG> v(in), w(out);
   const Planes<T, false> phf(phi, g.Ns, 1), mf(mu, g.Ns, 1), pf(p, g.Ns, 1);
   const Planes<T, false> jf[3] = {{jx, g.Ns, 1}, {jy, g.Ns, 1}, {jz, g.Ns, 1}};
-  const TileAt o = tile_at<TX, TY, TZ>(g);
-  if (o.z0 >= g.nz) return;
+  const TileAt o = tile_at<BIG, TX, TY, TZ>(g);
+  if (BIG && o.z0 >= g.nz) return;
   const int t = threadIdx.x, lx = t % TX, ly = t / TX % TY, lz = t / (TX * TY);
   const int x = o.x0 + lx, y = o.y0 + ly, z = o.z0 + lz;
   const bool owns = x < g.nx && y < g.ny && z < g.nz;
@@ -467,7 +477,7 @@ __global__ __launch_bounds__(NT) void k3_tile_step(
   __shared__ T lp[R1::A];
   const PopView<P, BIG> v(in), w(out);
   const Planes<T, false> phf(phi, g.Ns, 1);
-  const TileAt o = tile_at<TX, TY, TZ>(g);
+  const TileAt o = tile_at<BIG, TX, TY, TZ>(g);
   const int t = threadIdx.x;
   int lx = 0, ly = 0, lz = 0;
   if (t < NI) {
