@@ -662,6 +662,60 @@ struct MomentOut3 {
          *mu = nullptr;
 };
 
+// phi and the moments by rows, 64 nodes of a row to a wave (moments_rows,
+// phi_rows).
+template <int P, bool BIG>
+__global__ __launch_bounds__(256) void k3_phi(Pop3<P> in, typename PrecT<P>::T* __restrict__ phi,
+                                              Geom3 g, uint32_t nxc) {
+  using T = typename PrecT<P>::T;
+  const PopView<P, BIG> v(in);
+  const Planes<T, false> out(phi, g.Ns, 1);
+  for_rows<sizeof(T)>(g, nxc, [&](const RowCtx& R, const Lane& L) {
+    if constexpr (FixedG<P>::value) {
+      int32_t q = 0;
+#pragma unroll
+      for (int i = 0; i < 19; ++i) {
+        const Src s = pull_at(i, R, L);
+        q += v.g.ld(s.plane, s.row, s.vo);
+      }
+      out.st(0, R.rb[1][1], L.xo[1], T(q) * T(GQI));
+    } else {
+      T a = T(0);
+#pragma unroll
+      for (int i = 0; i < 19; ++i) {
+        const Src s = pull_at(i, R, L);
+        a += v.g.ld(s.plane, s.row, s.vo);
+      }
+      out.st(0, R.rb[1][1], L.xo[1], a);
+    }
+  });
+}
+
+template <int P, bool BIG>
+__global__ __launch_bounds__(256) void k3_macro(Pop3<P> in, const typename PrecT<P>::T* __restrict__ phi,
+                                                const typename PrecT<P>::T* __restrict__ mu,
+                                                MomentOut3 mo, Coef3<typename PrecT<P>::T> k,
+                                                Geom3 g, uint32_t nxc) {
+  using T = typename PrecT<P>::T;
+  const PopView<P, BIG> v(in);
+  const Planes<T, false> ph(phi, g.Ns, 1), mf(mu, g.Ns, 1);
+  for_rows<sizeof(T)>(g, nxc, [&](const RowCtx& R, const Lane& L) {
+    T f[19];
+    Node3<T> m;
+    node_state_r<P, BIG>(v, ph, mf, R, L, k, f, m);
+    // the pressure formed here: left to the branch that stores it, its inputs
+    // stayed live past the others' (149 registers, 3 waves per SIMD; 69, 7)
+    asm volatile("" : "+v"(m.p));
+    const uint32_t n = R.rb[1][1] + L.x;
+    if (mo.phi) mo.phi[n] = double(m.phi);
+    if (mo.rho) mo.rho[n] = double(m.rho);
+    for (int a = 0; a < 3; ++a)
+      if (mo.u[a]) mo.u[a][n] = double(m.u[a]);
+    if (mo.p) mo.p[n] = double(m.p);
+    if (mo.mu) mo.mu[n] = double(m.mu);
+  });
+}
+
 // Q2.29 sum of the pulled g words of every node (the order parameter the
 // fused FP32 step reads in its stage A).
 template <bool BIG>
@@ -1500,18 +1554,36 @@ void launch_tile_phi(lbm3_ctx* c, TL) {
                      Fields3<typename PrecT<P>::T>(c).phi, g);
 }
 
-template <int P>
-hipError_t phi_p(lbm3_ctx* c) {
-  return with_tile<P>(c->geom, [&](auto tl) { launch_tile_phi<P>(c, tl); });
+// phi by rows where it is the faster on its own: large lattices (us, rows and
+// tiles: fp64 256^3 522 and 543; totals, fp32 192^3 367 and 390, 48 x 256 x 256 200 and
+// 209, 500 x 500 x 16 220 and 227; but 300 x 300 x 17 123 and 114,
+// 1000 x 1000 x 3 369 and 352, where whole waves fall on rows beyond ny or nz).
+bool phi_rows(const Geom3& g) {
+  return g.N > 2500000 && g.nx >= 48 && g.ny >= 16 && g.nz >= 16;
 }
 
-// phi and mu fields of the current state.
 template <int P>
-hipError_t fields_p(lbm3_ctx* c) {
+hipError_t phi_p(lbm3_ctx* c, bool rows) {
+  const Geom3& g = c->geom;
+  if (!rows) return with_tile<P>(g, [&](auto tl) { launch_tile_phi<P>(c, tl); });
+  const Pop3<P> in{c->pop[c->cur], g.Ns};
+  auto* const phi = Fields3<typename PrecT<P>::T>(c).phi;
+  if (big3<P>(g))
+    hipLaunchKernelGGL((k3_phi<P, true>), dim3(row_grid(g)), dim3(256), 0, c->stream, in, phi, g,
+                       chunks_x(g));
+  else
+    hipLaunchKernelGGL((k3_phi<P, false>), dim3(row_grid(g)), dim3(256), 0, c->stream, in, phi, g,
+                       chunks_x(g));
+  return hipGetLastError();
+}
+
+// phi and mu fields of the current state, phi by rows or tiles.
+template <int P>
+hipError_t fields_p(lbm3_ctx* c, bool rows) {
   using T = typename PrecT<P>::T;
   const Geom3& g = c->geom;
   const Fields3<T> fl(c);
-  if (phi_p<P>(c) != hipSuccess) return hipErrorLaunchFailure;
+  if (phi_p<P>(c, rows) != hipSuccess) return hipErrorLaunchFailure;
   // segments of 32 planes, shorter on a lattice with too few columns for one
   // workgroup per CU (32^3: eight workgroups 36 us, 64 of four planes 5 us)
   int zs = MZ_ZS;
@@ -1693,11 +1765,38 @@ lbm_status step_p(lbm3_ctx* c, int64_t n) {
   return LBM_OK;
 }
 
+// FP64 moments by rows, with mu as a field. The halo that a tile shares with the
+// tiles above it is read again from memory once a layer of tiles exceeds the
+// cache, and a lattice of three layers leaves a quarter of a tile's lanes idle
+// (us, rows and tiles: 256^3 1270 and 1409, 500 x 500 x 16 330 and 355, 500 x 500 x 8
+// 168 and 179, 192^3 622 and 631, 1000 x 1000 x 3 249 and 304, 1000 x 3 x 1000 266 and
+// 314; but 256 x 256 x 48 305 and 302, 64 x 300 x 300 527 and 517, 250 x 100 x 100 280
+// and 248, 140^3 285 and 263; FP32 256^3 837 and 686).
+bool moments_rows(const Geom3& g) {
+  const int64_t rows = (int64_t)chunks_x(g) * 64 * g.ny * g.nz, tl = tile_lanes(g);
+  const int64_t layer = (int64_t)g.nx * g.ny;
+  if (g.N < 1900000 || rows > tl) return false;
+  return layer >= 200000 || (layer >= 36000 && g.N > 4000000) || 5 * rows <= 4 * tl;
+}
+
 template <int P>
 lbm_status moments_p(lbm3_ctx* c, const MomentOut3& mo) {
   using T = typename PrecT<P>::T;
   const Geom3& g = c->geom;
   const Pop3<P> in{c->pop[c->cur], g.Ns};
+  if constexpr (P == P_F64) {
+    if (moments_rows(g)) {
+      if (fields_p<P>(c, true) != hipSuccess) return LBM_EDEVICE;
+      const Fields3<T> fl(c);
+      if (big3<P>(g))
+        hipLaunchKernelGGL((k3_macro<P, true>), dim3(row_grid(g)), dim3(256), 0, c->stream, in,
+                           (const T*)fl.phi, (const T*)fl.mu, mo, coef3<T>(c), g, chunks_x(g));
+      else
+        hipLaunchKernelGGL((k3_macro<P, false>), dim3(row_grid(g)), dim3(256), 0, c->stream, in,
+                           (const T*)fl.phi, (const T*)fl.mu, mo, coef3<T>(c), g, chunks_x(g));
+      return st(hipGetLastError());
+    }
+  }
   return st(with_tile<P>(g, [&](auto tl) {
     using TL = decltype(tl);
     launch_tile_phi<P>(c, tl);
@@ -1711,7 +1810,7 @@ template <int P>
 lbm_status mass_p(lbm3_ctx* c) {
   using T = typename PrecT<P>::T;
   const Geom3& g = c->geom;
-  if (fields_p<P>(c) != hipSuccess) return LBM_EDEVICE;
+  if (fields_p<P>(c, phi_rows(c->geom)) != hipSuccess) return LBM_EDEVICE;
   Pop3<P> in{c->pop[c->cur], g.Ns};
   const T* phi = (const T*)c->fields;
   const T* mu = (const T*)(c->fields + g.Ns * 8);
