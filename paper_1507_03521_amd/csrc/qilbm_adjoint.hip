@@ -1087,7 +1087,9 @@ AdjShape adj_shape(AdjointState& a, const Geom& g) {
 // Tiles of the tiled step, 0 where the row sweep runs.
 template <typename T>
 int adj_tiles(AdjointState& a, const Geom& g) {
-  return adj_tile_fits<T>(g, adj_shape<T>(a, g)) ? adj_tile_count<T>(g) : 0;
+  if (!adj_tile_fits<T>(g)) return 0;
+  if (g.nx > ADJ_LONG_ROWS && !adj_tiles_beat_rows<T>(g, adj_shape<T>(a, g))) return 0;
+  return adj_tile_count<T>(g);
 }
 
 // One adjoint step from the record of forward step t.

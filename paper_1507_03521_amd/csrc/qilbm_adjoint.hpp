@@ -62,7 +62,12 @@ struct AdjShape {
 // (adj_tile_fits): replaces the cotangents hin by hout and adds each tile's
 // four parameter sums to its slot of part (adj_tile_count tiles).
 template <typename T>
-bool adj_tile_fits(const Geom& g, const AdjShape& sh);
+bool adj_tile_fits(const Geom& g);
+// Whether they are also the faster ones on a lattice of rows longer than
+// ADJ_LONG_ROWS columns, which the row sweep would step in shape sh.
+constexpr int ADJ_LONG_ROWS = 8192;
+template <typename T>
+bool adj_tiles_beat_rows(const Geom& g, const AdjShape& sh);
 template <typename T>
 int adj_tile_count(const Geom& g);
 template <typename T>

@@ -304,17 +304,19 @@ Shape shape(const Geom& g) {
 // Infinity Cache holds (us per step, tiles against the row sweep): fp64 490 k
 // nodes (165 MB) 54 and 127, 810 k (272 MB) 92 and 130, 1.0 M (336 MB) 136 and 158,
 // 1.2 M (407 MB) 177 and 169; fp32 934 k (157 MB) 60 and 83, 2.0 M (337 MB) 159 and
-// 122. It also keeps the byte offsets in a buffer below 2^31. Of rows of more than
-// 8192 columns, few fit, which give the row sweep (sh) short segments: it then
-// has the shorter time where the tiles' lanes, idle ones included, exceed what
-// its rounds of workgroups take (sweep and tiles: fp32 22 222 x 9 44 and 25,
-// 66 666 x 9 54 and 63, 40 000 x 25 92 and 81, 52 000 x 25 92 and 104; fp64 35 294 x 17
-// 106 and 77, 58 823 x 17 118 and 159).
+// 122. It also keeps the byte offsets in a buffer below 2^31.
 template <typename T>
-bool adj_tile_fits(const Geom& g, const AdjShape& sh) {
-  if ((2 * 18 + 6) * g.Ns * (int64_t)sizeof(T) > (int64_t)(sizeof(T) == 8 ? 325 : 256) << 20)
-    return false;
-  if (g.nx <= 8192) return true;
+bool adj_tile_fits(const Geom& g) {
+  return (2 * 18 + 6) * g.Ns * (int64_t)sizeof(T) <= (int64_t)(sizeof(T) == 8 ? 325 : 256) << 20;
+}
+
+// Of rows of more than 8192 columns, few fit, which give the row sweep short
+// segments: it then has the shorter time where the tiles' lanes, idle ones
+// included, exceed what its rounds of workgroups take (sweep and tiles: fp32
+// 22 222 x 9 44 and 25, 66 666 x 9 54 and 63, 40 000 x 25 92 and 81, 52 000 x 25 92 and
+// 104; fp64 35 294 x 17 106 and 77, 58 823 x 17 118 and 159).
+template <typename T>
+bool adj_tiles_beat_rows(const Geom& g, const AdjShape& sh) {
   const int64_t rounds = ((int64_t)sh.nstrips * sh.nseg + sh.resident - 1) / sh.resident;
   const int64_t lanes =
       sizeof(T) == 8 ? tiles(g, 16, 8) * (int64_t)128 : tiles(g, 32, 8) * (int64_t)256;
@@ -345,7 +347,8 @@ hipError_t launch_adj_tile(const void* rec, const void* hin, void* hout, double*
 }
 
 #define QILBM_INSTANTIATE(T)                                                                     \
-  template bool adj_tile_fits<T>(const Geom&, const AdjShape&);                                  \
+  template bool adj_tile_fits<T>(const Geom&);                                                   \
+  template bool adj_tiles_beat_rows<T>(const Geom&, const AdjShape&);                            \
   template int adj_tile_count<T>(const Geom&);                                                   \
   template hipError_t launch_adj_tile<T>(const void*, const void*, void*, double*,               \
                                          const Coef<T>&, const Geom&, hipStream_t);
