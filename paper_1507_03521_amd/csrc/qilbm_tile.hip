@@ -328,8 +328,9 @@ __device__ __forceinline__ void tile_phase(__amdgpu_buffer_rsrc_t rin, __amdgpu_
     macro_node(ph, mu, gphx, gphy, gmux, gmuy, lapmu, S, jx, jy, c, m);
     L.p[e] = m.p;
     if (rec && owns) {
-      const T v[6] = {ph, mu, m.p, S, jx, jy};
-      if (rec_stream) {
+      // two steps a launch, or stores written through: lattices too small for it
+      if (POL == ST_BACK && !FROM_MID && !TO_MID && rec_stream) {
+        const T v[6] = {ph, mu, m.p, S, jx, jy};
         const uint32_t pb = Ns * (uint32_t)sizeof(T);
         const __amdgpu_buffer_rsrc_t rr =
             __builtin_amdgcn_make_buffer_rsrc(rec, 0, (int)(6 * pb), BUF_WORD3);
@@ -337,8 +338,12 @@ __device__ __forceinline__ void tile_phase(__amdgpu_buffer_rsrc_t rin, __amdgpu_
         for (int q = 0; q < 6; ++q)
           buf_st<T, ST_STREAM>(v[q], rr, (uint32_t)n * (uint32_t)sizeof(T), q * pb);
       } else {
-#pragma unroll
-        for (int q = 0; q < 6; ++q) rec[q * g.Ns + n] = v[q];
+        rec[n] = ph;
+        rec[g.Ns + n] = mu;
+        rec[2 * g.Ns + n] = m.p;
+        rec[3 * g.Ns + n] = S;
+        rec[4 * g.Ns + n] = jx;
+        rec[5 * g.Ns + n] = jy;
       }
     }
   }
