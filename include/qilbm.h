@@ -149,7 +149,10 @@ lbm_status lbm_step(lbm_ctx* ctx, int64_t nsteps);
 
 /* Macroscopic fields at the current time t (Sec. III moments): phi, rho,
  * u = (ux, uy), p and mu, each FP64 [ny][nx] device arrays; any pointer
- * may be NULL to skip that field. Asynchronous. */
+ * may be NULL to skip that field. They are formed in the arithmetic of the
+ * storage type (FP16 storage: binary32); phi is the sum of the stored g, in
+ * FP32 and FP16 storage exact but for one rounding to binary32 while the
+ * populations take at most 4 GiB. Asynchronous. */
 lbm_status lbm_moments(lbm_ctx* ctx, double* phi_dev, double* rho_dev,
                        double* ux_dev, double* uy_dev, double* p_dev,
                        double* mu_dev);
@@ -251,14 +254,17 @@ lbm_status lbm_set_stream(lbm_ctx* ctx, void* stream);
 
 /* Launch shape of the one-step fused kernel: rows per workgroup segment
  * (0 = automatic: about 2.25 workgroups per resident slot, 16..32 rows; a
- * lattice whose two population buffers fit in 256 MiB then runs a tiled
- * kernel instead of this row-sweeping one). Results do not depend on it
- * beyond rounding. */
+ * lattice whose two population buffers stay in the cache, up to 220 MiB in
+ * FP64, 256 in FP32 and 224 in FP16 storage and less where rows are longer
+ * than 2048 columns, then runs a tiled kernel instead of this row-sweeping
+ * one; a number of rows always selects the row sweep). Results do not depend
+ * on the number, and on the kernel only by rounding. */
 lbm_status lbm_set_launch(lbm_ctx* ctx, int32_t seg_rows);
 
-/* Current one-step fused launch shape into out[4] (host): column strips (of
+/* Current launch shape of the row-sweeping one-step kernel into out[4]
+ * (host), also where a tiled kernel runs (lbm_set_launch): column strips (of
  * equal width, at most 250 columns), segments per strip, rows per segment,
- * threads per workgroup. lbm_step_record always uses this kernel. */
+ * threads per workgroup. lbm_step_record takes the kernels of one step. */
 lbm_status lbm_launch_info(const lbm_ctx* ctx, int32_t out[4]);
 
 /* Time steps per pass of the fused kernel in lbm_step (temporal blocking,
@@ -275,9 +281,10 @@ lbm_status lbm_launch_info(const lbm_ctx* ctx, int32_t out[4]);
  * same expressions, but the compiler may fuse multiply-adds differently in
  * each. The exact integer invariant of the stored g holds in both. seg_rows: rows per workgroup
  * segment of the two-step kernel (0 = automatic: one round of workgroups; a
- * lattice whose two population buffers fit in 256 MiB then runs a pair of
- * FP64 or FP32 steps in tiled kernels instead, as one launch or, above about
- * 256 x 256 nodes, as two).
+ * lattice whose two population buffers stay in the cache, up to 220 MiB in
+ * FP64 and 224 in FP32 and less where rows are longer than 2048 columns, then
+ * runs a pair of steps in tiled kernels instead, as one launch or, above about
+ * 256 x 256 nodes, as two; a number of rows always selects the row sweep).
  * LBM_EINVAL for steps other than 1 and 2, or seg_rows < 0. Applies to lbm_step only (not lbm_step_record, not
  * LBM_FLAG_UNFUSED). */
 lbm_status lbm_set_pass(lbm_ctx* ctx, int32_t steps, int32_t seg_rows);
@@ -285,7 +292,8 @@ lbm_status lbm_set_pass(lbm_ctx* ctx, int32_t steps, int32_t seg_rows);
 /* Shape of the row-sweeping kernel for a pair of steps, which lbm_step
  * launches except where a tiled kernel runs (lbm_set_pass), into out[5]
  * (host): steps per pass, column strips (at most 242 columns for two steps),
- * segments per strip, rows per segment, threads per workgroup. */
+ * segments per strip, rows per segment, threads across a strip (a workgroup
+ * of FP64 has a set of them for each of the two steps). */
 lbm_status lbm_pass_info(const lbm_ctx* ctx, int32_t out[5]);
 
 /* ---------------------------------------------------------------- adjoint

@@ -562,14 +562,15 @@ __global__ __launch_bounds__(256) void k_hat_to(const T* __restrict__ hat, doubl
 //   0:  record row r (phi, mu, p, S, jx, jy) into the rings
 //   A': collision transpose of row r - d (post-collision cotangents gathered
 //       from the incoming cotangents, prefetched by the previous iteration);
-//       grad p cotangent into LDS, the rest kept in registers
+//       grad p cotangent into LDS, the rest kept in registers; the gathers of
+//       row r's g cotangents go out for the next iteration
 //   B': pressure cotangent of row r - 2d (grad^T of the grad p cotangents of
 //       rows r - 3d .. r - d), the macroscopic transposes, f cotangents out;
-//       grad mu, lambda D and grad phi cotangents into LDS
-//   C': mu cotangent of row r - 3d (grad^T, lap^T), then mu(phi)
-//   D': phi cotangent of row r - 4d (grad^T, lap^T), g cotangents out; the
-//       gathers of row r's post-collision cotangents and the record row
-//       r + d are issued here for the next iteration.
+//       grad mu, lambda D and grad phi cotangents into LDS; the gathers of
+//       row r's f cotangents go out
+//   C': the loads of record row r + d go out; mu cotangent of row r - 3d
+//       (grad^T, lap^T), then mu(phi)
+//   D': phi cotangent of row r - 4d (grad^T, lap^T), g cotangents out
 // Stage s (A' = 1 ... D' = 4) runs on lanes [s, wi + 8 - s) and rows
 // [y0 - 4 + s, y1 + 4 - s); the record rows reach 4 beyond the segment.
 constexpr int AH = 4;

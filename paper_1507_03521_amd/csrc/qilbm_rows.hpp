@@ -42,10 +42,9 @@ template <> struct BufT<P_F32> { using F = float; using G0 = int32_t; using GR =
 template <> struct BufT<P_F16> { using F = __half; using G0 = int32_t; using GR = uint32_t; using R = uint32_t; };
 
 // BIG: a group of population planes (f_0..8 or g_1..8) spans 4 GiB or more,
-// beyond the 32-bit range of one descriptor (FP64: more than 2 GiB, see
-// fused_big); every access then builds a
-// descriptor for its own plane (scalar work only) and the scalar offset
-// holds the row alone.
+// beyond the 32-bit range of one descriptor (fused_big); every access then
+// builds a descriptor for its own plane (scalar work only) and the scalar
+// offset holds the row alone.
 template <int P, bool BIG = false>
 struct BufPop {
   using T = typename PrecT<P>::T;

@@ -611,7 +611,10 @@ void launch_tile(const void* pin, void* pout, const Coef<typename PrecT<P>::T>& 
 // 640 x 1000 34.4 and 33.9 to 35.0: the end is a small part by then). A row that does not start on a 128-byte line has its tiles share
 // lines, which then are written in parts, twice (fp64 1001 x 700 36.6, 40.0
 // through; fp32 701 x 1333 25.9, 27.4), and still gains while the lattice is
-// small (fp64 500 x 500 16.5, 15.0; 301 x 701 14.7, 14.3).
+// small (fp64 500 x 500 16.5, 15.0; 301 x 701 14.7, 14.3). FP16 storage, whose
+// words take 4 and 2 bytes, has such rows at nx % 32 and % 64, and yet the same
+// line: 560 x 560 10.2, 9.7; 400 x 1000 12.2, 11.5; 624 x 900 15.3, 15.0; 640 x 900
+// 15.6, 15.1; 701 x 800 15.1, 15.4; 1333 x 400 15.1, 15.3.
 bool tile_through(const Geom& g) {
   return g.N <= (g.nx % 16 == 0 ? 600000 : 300000);
 }
