@@ -256,7 +256,7 @@ lbm_status lbm_set_stream(lbm_ctx* ctx, void* stream);
  * (0 = automatic: about 2.25 workgroups per resident slot, 16..32 rows; a
  * lattice whose two population buffers stay in the cache, up to 220 MiB in
  * FP64, 256 in FP32 and 224 in FP16 storage and less where rows are longer
- * than 2048 columns, then runs a tiled kernel instead of this row-sweeping
+ * than 3072 columns, then runs a tiled kernel instead of this row-sweeping
  * one; a number of rows always selects the row sweep). Results do not depend
  * on the number, and on the kernel only by rounding. */
 lbm_status lbm_set_launch(lbm_ctx* ctx, int32_t seg_rows);
@@ -282,7 +282,7 @@ lbm_status lbm_launch_info(const lbm_ctx* ctx, int32_t out[4]);
  * each. The exact integer invariant of the stored g holds in both. seg_rows: rows per workgroup
  * segment of the two-step kernel (0 = automatic: one round of workgroups; a
  * lattice whose two population buffers stay in the cache, up to 220 MiB in
- * FP64 and 224 in FP32 and less where rows are longer than 2048 columns, then
+ * FP64 and 224 in FP32 and less where rows are longer than 3072 columns, then
  * runs a pair of steps in tiled kernels instead, as one launch or, above about
  * 256 x 256 nodes, as two; a number of rows always selects the row sweep).
  * LBM_EINVAL for steps other than 1 and 2, or seg_rows < 0. Applies to lbm_step only (not lbm_step_record, not

@@ -320,7 +320,7 @@ bool adj_tiles_beat_rows(const Geom& g, const AdjShape& sh) {
   const int64_t rounds = ((int64_t)sh.nstrips * sh.nseg + sh.resident - 1) / sh.resident;
   const int64_t lanes =
       sizeof(T) == 8 ? tiles(g, 16, 8) * (int64_t)128 : tiles(g, 32, 8) * (int64_t)256;
-  return lanes <= (sizeof(T) == 8 ? 55000 : 74000) * rounds * (sh.seg + 3);
+  return lanes <= (sizeof(T) == 8 ? 48000 : 74000) * rounds * (sh.seg + 3);
 }
 
 template <typename T>

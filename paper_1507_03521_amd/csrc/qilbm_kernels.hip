@@ -1464,7 +1464,8 @@ hipError_t launch_moment_fields(const void* pop, void* phi, void* mu,
                                 const Coef<typename PrecT<P>::T>& c, const Geom& g,
                                 hipStream_t s) {
   using T = typename PrecT<P>::T;
-  if (!moments_fit<P>(g)) return launch_fields<P>(pop, phi, mu, c, g, s);
+  // FP64: k_phi adds the same nine in the same order
+  if (P == P_F64 || !moments_fit<P>(g)) return launch_fields<P>(pop, phi, mu, c, g, s);
   const hipError_t e = launch_phi<P>(pop, (T*)phi, g, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_mu<T>, dim3(nblk(g.N, 256)), dim3(256), 0, s, (const T*)phi, (T*)mu, c, g);

@@ -636,19 +636,19 @@ hipError_t launch_tile_variant(const void* pin, void* pout, const Coef<typename 
 
 }  // namespace
 
-// Rows of more than 2048 columns (FP32 4 MB of populations in eight rows): the
+// Rows of more than 3072 columns (FP32 1.7 MB of populations in eight rows): the
 // halo rows of a tile have left its XCD's L2 when the tiles below need them,
 // and a lattice of few rows gives the sweep short segments, so it has the
 // shorter time already at smaller sizes. The sweep takes (rows per segment +
 // warm-up) for each round of its workgroups, the tiles a time by the lane,
-// idle ones included; us per step, sweep and tiles: fp32 4095 x 341 44.6 and 45.1, x
-// 424 45 and 55; 24 390 x 41 43 and 36, 31 707 x 41 43 and 46; 50 000 x 12 25 and 22,
+// idle ones included; us per step, sweep and tiles: fp32 4095 x 290 44.5 and 39, x
+// 341 44.6 and 45.1, x 424 45 and 55; 24 390 x 41 43 and 36, 31 707 x 41 43 and 46; 50 000 x 12 25 and 22,
 // 83 333 x 12 29 and 35; 22 222 x 9 20 and 12, 66 666 x 9 24 and 26; fp16 4095 x 610
 // 59 and 55; 83 333 x 12 36 and 30, 133 333 x 12 43 and 45; 200 000 x 3 20 and 30;
-// fp64 40 000 x 5 21 and 18, 120 000 x 5 42 and 47.
+// fp64 40 000 x 5 21 and 18, 120 000 x 5 42 and 47, 50 000 x 12 37.5 and 37.7.
 template <int P>
 bool tiles_beat_rows(const Geom& g) {
-  if (g.nx <= 2048) return true;
+  if (g.nx <= 3072) return true;
   if constexpr (P == P_F16) {
     const FusedShape sh = fused_shape<P>(g, 0, 0);
     const int64_t wgs = (int64_t)sh.nstrips * sh.nseg;
@@ -658,9 +658,9 @@ bool tiles_beat_rows(const Geom& g) {
     const FusedShape sh = fused2_shape<P>(g, 0, resident);
     const int64_t rounds = ((int64_t)sh.nstrips * sh.nseg + resident - 1) / resident;
     if constexpr (P == P_F64)
-      return tiles(g, 32, 4) * (int64_t)128 <= 42000 * rounds * (sh.seg_rows + 4);
+      return tiles(g, 32, 4) * (int64_t)128 <= 37000 * rounds * (sh.seg_rows + 4);
     return 2 * pop_bytes(P, g.Ns) <= (int64_t)205 << 20 &&
-           tiles(g, 32, 8) * (int64_t)256 <= 70000 * rounds * (sh.seg_rows + 5);
+           tiles(g, 32, 8) * (int64_t)256 <= 66500 * rounds * (sh.seg_rows + 5);
   }
 }
 
@@ -775,12 +775,12 @@ hipError_t launch_moments(const void* pop, const MomentOut& mo,
   return hipGetLastError();
 }
 
-// Totals likewise, from 600 thousand lanes on (us, tiles against a node per
+// Totals likewise, from 400 thousand lanes on (us, tiles against a node per
 // thread, fp64: 1 M nodes, nx = 3 158 and 70, 8 81 and 70, 10 71 and 70, 12 65
-// and 70; 200 k, 3 58 and 40, 10 41 and 40; 40 k, 3 35 and 37).
+// and 70; 200 k, 3 58 and 40, 10 41 and 40; 40 k, 3 35 and 33, 4 32 and 35).
 bool mass_tiled(const Geom& g) {
   const int64_t lanes = tiles(g, MASS_TX, MASS_TY) * (int64_t)(MASS_TX * MASS_TY);
-  return lanes <= 600000 || lanes <= 3 * g.N;
+  return lanes <= 400000 || lanes <= 3 * g.N;
 }
 
 // Workgroups of the totals kernel, one partial each.
